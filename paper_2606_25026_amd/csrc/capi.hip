@@ -20,9 +20,9 @@ hipError_t conv_forward_layer(hipStream_t s, int layer, const uint16_t* in, cons
 hipError_t conv_backward_data(hipStream_t s, int layer, const uint16_t* dz, const uint16_t* wbwd,
                               const uint16_t* act_in, uint16_t* dact, int n);
 hipError_t conv_backward_weight(hipStream_t s, int layer, const uint16_t* dz,
-                                const uint16_t* act_in, float* part, int nblocks, float* out,
-                                int n);
-int wgrad_row(int layer);
+                                const uint16_t* act_in, float* part, int max_blocks, float* gw,
+                                float* gb, int n);
+int wgrad_part_floats();
 hipError_t net_pack_input(hipStream_t s, const float* x, uint16_t* y, int64_t cells, int cin,
                           int cp, const double* scales);
 hipError_t net_mse(hipStream_t s, const float* y, const float* t, uint16_t* dy, double* part,
@@ -46,8 +46,6 @@ hipError_t net_moments(hipStream_t s, const float* x, const float* y, int64_t ce
 hipError_t net_fit_scales(hipStream_t s, const double* rows, double count, double* scal);
 hipError_t net_set_scales(hipStream_t s, double* scal, double s_psi, double s_phi, double s_out);
 size_t net_moment_doubles();
-hipError_t net_unpack_grads(hipStream_t s, const float* sum, float* gw, float* gb, int cin,
-                            int cout, int cpin, int row);
 hipError_t launch_restrict_modes(hipStream_t s, const void* fine, void* coarse, int nf, int nc,
                                  int prec);
 hipError_t launch_contrast(const Launch& L, int prec, int64_t n);
@@ -1561,7 +1559,7 @@ int net_params() {
 int net_kpad(int cp) { return (27 * cp + 15) / 16 * 16; }
 
 struct NetLayout {
-    size_t params, grads, am, av, wf[3], wb[3], x0, a1, a2, y, dy, d2, d1, wpart, wsum[3], dpart,
+    size_t params, grads, am, av, wf[3], wb[3], x0, a1, a2, y, dy, d2, d1, wpart, dpart,
         mom, scal, total;
 };
 
@@ -1585,8 +1583,7 @@ NetLayout net_layout(int n) {
     L.dy = c.take(cells * 4 * 2);
     L.d2 = c.take(cells * 16 * 2);
     L.d1 = c.take(cells * 16 * 2);
-    L.wpart = c.take(size_t(kNetWgradBlocks) * 16 * wgrad_row(1) * 4);
-    for (int l = 0; l < kNetLayers; ++l) L.wsum[l] = c.take(16 * wgrad_row(l) * 4);
+    L.wpart = c.take(size_t(kNetWgradBlocks) * wgrad_part_floats() * 4);
     L.dpart = c.take(1024 * 8);
     L.mom = c.take(net_moment_doubles() * 8);
     L.scal = c.take(8 * 8);
@@ -1666,14 +1663,10 @@ hipError_t net_run_backward(wdm_net* net) {
     const uint16_t* act[3] = {net->at<uint16_t>(net->L.x0), net->at<uint16_t>(net->L.a1),
                               net->at<uint16_t>(net->L.a2)};
     for (int l = kNetLayers - 1; l >= 0; --l) {
-        if ((e = conv_backward_weight(s, l, dz[l], act[l], net->at<float>(net->L.wpart),
-                                      kNetWgradBlocks, net->at<float>(net->L.wsum[l]), n)) !=
-            hipSuccess)
-            return e;
         float* gw = net->at<float>(net->L.grads) + net->param_off(l);
         float* gb = gw + size_t(kNetCout[l]) * kNetCin[l] * 27;
-        if ((e = net_unpack_grads(s, net->at<float>(net->L.wsum[l]), gw, gb, kNetCin[l],
-                                  kNetCout[l], kNetCpIn[l], wgrad_row(l))) != hipSuccess)
+        if ((e = conv_backward_weight(s, l, dz[l], act[l], net->at<float>(net->L.wpart),
+                                      kNetWgradBlocks, gw, gb, n)) != hipSuccess)
             return e;
         if (l > 0 &&
             (e = conv_backward_data(s, l, dz[l], net->at<uint16_t>(net->L.wb[l]), act[l],

@@ -280,86 +280,384 @@ __global__ __launch_bounds__(256, 3) void k_conv(const uint16_t* __restrict__ in
     }
 }
 
-// Weight gradient partials.  dz: bf16 [cells][CPZ] (gradient at this layer's
-// pre-activation, COUT real channels); act: bf16 [cells][CPIN] (layer input).
-// Each work-group sums `chunk` cells and writes
-//   part[wg][m][k]  = sum_p dz[p][m] act[p + tap(k)][c(k)]   (m < 16, k < KC*16)
-//   part[wg][m][KC*16] = sum_p dz[p][m]                        (bias gradient)
-// GEMM roles: M = output channel, N = k, K = cells (16 per MFMA).
-template <int CPIN, int CPZ>
-__global__ __launch_bounds__(256) void k_conv_wgrad(const uint16_t* __restrict__ dz,
-                                                    const uint16_t* __restrict__ act,
-                                                    float* __restrict__ part, int n,
-                                                    int64_t chunk) {
-    constexpr int KC = (27 * CPIN + 15) / 16;
-    constexpr int ROW = KC * 16 + 1;
-    __shared__ float red[16 * ROW];
-    const Grid3 g{n};
-    const int lane = int(threadIdx.x) & 63;
-    const int wave = int(threadIdx.x) >> 6;
-    for (int i = int(threadIdx.x); i < 16 * ROW; i += 256) red[i] = 0.0f;
-    __syncthreads();
-    f32x4 acc[KC];
-#pragma unroll
-    for (int t = 0; t < KC; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float bsum = 0.0f;
-    const int m = lane & 15;      // A row (output channel)
-    const int kq = lane >> 4;     // cells 4*kq .. 4*kq+3 of the 16-cell K block
-    const int64_t c0 = int64_t(blockIdx.x) * chunk;
-    const int64_t c1 = c0 + chunk < g.cells() ? c0 + chunk : g.cells();
-    for (int64_t blk = c0 + int64_t(wave) * 16; blk < c1; blk += 64) {
-        bf16x4 a;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int64_t p = blk + 4 * kq + q;
-            uint16_t v = 0;
-            if (p < c1 && m < CPZ) v = gldr(dz, p * CPZ + m);
-            a[q] = short(v);
-            bsum += bf2f(v);
-        }
-#pragma unroll
-        for (int t = 0; t < KC; ++t) {
-            const int k = t * 16 + m;          // B column (lane % 16)
-            bf16x4 b = {0, 0, 0, 0};
-            if (k < 27 * CPIN) {
-                const int tap = k / CPIN, c = k % CPIN;
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int64_t p = blk + 4 * kq + q;
-                    if (p < c1) b[q] = short(gldr(act, g.shift(p, tap) * CPIN + c));
-                }
-            }
-            acc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc[t], 0, 0, 0);
+// ---------------------------------------------------------------------------
+// Weight gradients.  gw[m][c][tap] = sum_p dz[p][m] act[p + tap][c] is a GEMM
+// whose K dimension is the cells; both operands are stored channels last, so
+// the K index runs across memory.  What bounded the direct form (each lane
+// gathering its operand two bytes at a time from global memory, neighbour
+// indices by 64-bit division) was the load instructions: 1.65 / 5.92 / 5.93 ms
+// for the three layers at 128^3.  Here a work-group stages a brick of both
+// operands in LDS transposed to [channel][x][y][z] once per tile and every tap
+// reads it from there: a lane's eight K values are eight neighbouring z of one
+// channel, one 16-byte LDS read for v_mfma_f32_16x16x32_bf16.
+// ---------------------------------------------------------------------------
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+
+// 4 x 4 x 32 cells per tile; bricks with the one-cell periodic halo.
+constexpr int kGX = 4, kGY = 4, kGZ = 32;
+constexpr int kGBX = kGX + 2, kGBY = kGY + 2, kGRows = kGBX * kGBY;
+constexpr int kGWaves = 8, kGThreads = 64 * kGWaves;
+// bytes of one z row in LDS (32 cells, two halo cells, padding) and of one
+// channel: odd multiples of 16 bytes, so that sixteen channels read at once
+// fall on different banks
+constexpr int kGRow = 80;
+constexpr int kGChanIn = kGRows * kGRow + 16;        // haloed brick
+constexpr int kGChanOut = kGX * kGY * kGRow + 16;    // the tile's own cells
+
+__device__ __forceinline__ bf16x8 lds_b128(const uint8_t* p) {
+    const u32x4 w = *reinterpret_cast<const u32x4*>(p);
+    bf16x8 r;
+    __builtin_memcpy(&r, &w, sizeof(r));
+    return r;
+}
+__device__ __forceinline__ bf16x8 as_bf16x8(u32x4 w) {
+    bf16x8 r;
+    __builtin_memcpy(&r, &w, sizeof(r));
+    return r;
+}
+// (a, b) hold 8 channels of the cells z and z + 1; word k of the result pairs
+// channel k of both: (z | z + 1 << 16)
+__device__ __forceinline__ uint32_t pair_channel(u32x4 a, u32x4 b, int k) {
+    const uint32_t x = a[k >> 1], y = b[k >> 1];
+    return (k & 1) ? __builtin_amdgcn_perm(y, x, 0x07060302u) : __builtin_amdgcn_perm(y, x, 0x05040100u);
+}
+
+struct GTile {
+    int x0, y0, z0;
+    __device__ __forceinline__ GTile(int64_t t, int ty, int tz) {
+        const int64_t r = t / tz;
+        z0 = int(t - r * tz) * kGZ;
+        const int64_t q = r / ty;
+        y0 = int(r - q * ty) * kGY;
+        x0 = int(q) * kGX;
+    }
+};
+
+// 16-channel operand without halo: item i = ((row * 16) + pair) * 2 + half,
+// one item per thread; cells past the grid give zeros.
+static_assert(kGX * kGY * (kGZ / 2) * 2 == kGThreads, "one item per thread");
+struct OutRegs {
+    u32x4 a, b;
+    __device__ __forceinline__ void load(const uint16_t* __restrict__ src, const GTile& t, int n) {
+        const int i = int(threadIdx.x), half = i & 1, pair = (i >> 1) & 15, row = i >> 5;
+        const int x = t.x0 + row / kGY, y = t.y0 + row % kGY, z = t.z0 + 2 * pair;
+        a = b = u32x4{0u, 0u, 0u, 0u};
+        if (x < n && y < n) {
+            const uint16_t* p = src + ((int64_t(x) * n + y) * n + z) * 16 + half * 8;
+            if (z < n) a = *(const WDM_GAS u32x4*)p;
+            if (z + 1 < n) b = *(const WDM_GAS u32x4*)(p + 16);
         }
     }
-    // D: lane holds [row 4*kq + q][col lane % 16] of every tile; sum the waves in LDS
-    // in a fixed order
-    for (int w = 0; w < 4; ++w) {
-        if (wave == w) {
+    __device__ __forceinline__ void store(uint8_t* lds) const {
+        const int i = int(threadIdx.x), half = i & 1, pair = (i >> 1) & 15, row = i >> 5;
+        uint8_t* p = lds + half * 8 * kGChanOut + row * kGRow + pair * 4;
 #pragma unroll
-            for (int t = 0; t < KC; ++t)
+        for (int k = 0; k < 8; ++k)
+            *reinterpret_cast<uint32_t*>(p + k * kGChanOut) = pair_channel(a, b, k);
+    }
+};
+
+// 16-channel operand with halo: items ((row * 17) + pair) * 2 + half of the
+// 6 x 6 x 34 brick.  Only halo cells wrap; cells beyond them are zeros.
+struct HaloRegs {
+    static constexpr int kPairs = kGZ / 2 + 1, kItems = kGRows * kPairs * 2;
+    static constexpr int kIt = (kItems + kGThreads - 1) / kGThreads;
+    u32x4 a[kIt], b[kIt];
+    __device__ __forceinline__ void load(const uint16_t* __restrict__ src, const GTile& t, int n) {
 #pragma unroll
-                for (int q = 0; q < 4; ++q) red[(4 * kq + q) * ROW + t * 16 + m] += acc[t][q];
-            // bias: lanes with the same m hold partial sums over different cells
-            float bs = bsum;
-            bs += __shfl_xor(bs, 16);
-            bs += __shfl_xor(bs, 32);
-            if (kq == 0) red[m * ROW + KC * 16] += bs;
+        for (int k = 0; k < kIt; ++k) {
+            const int i = int(threadIdx.x) + k * kGThreads;
+            a[k] = b[k] = u32x4{0u, 0u, 0u, 0u};
+            if (i >= kItems) continue;
+            const int half = i & 1, j = i >> 1, row = j / kPairs, pair = j - row * kPairs;
+            const int x = t.x0 + row / kGBY - 1, y = t.y0 + row % kGBY - 1, z = t.z0 + 2 * pair - 1;
+            if (x > n || y > n) continue;
+            const uint16_t* p =
+                src + (int64_t(wrap_edge(x, n)) * n + wrap_edge(y, n)) * n * 16 + half * 8;
+            if (z <= n) a[k] = *(const WDM_GAS u32x4*)(p + int64_t(wrap_edge(z, n)) * 16);
+            if (z < n) b[k] = *(const WDM_GAS u32x4*)(p + int64_t(wrap_edge(z + 1, n)) * 16);
+        }
+    }
+    __device__ __forceinline__ void store(uint8_t* lds) const {
+#pragma unroll
+        for (int k = 0; k < kIt; ++k) {
+            const int i = int(threadIdx.x) + k * kGThreads;
+            if (i >= kItems) continue;
+            const int half = i & 1, j = i >> 1, row = j / kPairs, pair = j - row * kPairs;
+            uint8_t* p = lds + half * 8 * kGChanIn + row * kGRow + pair * 4;
+#pragma unroll
+            for (int c = 0; c < 8; ++c)
+                *reinterpret_cast<uint32_t*>(p + c * kGChanIn) = pair_channel(a[k], b[k], c);
+        }
+    }
+};
+
+// 4-channel operand with halo, kept as three copies shifted by 0, 1 and 2
+// cells along z, so that every tap's read is 16-byte aligned: copy s holds
+// cell z0 - 1 + i + s at position i.
+struct Halo4Regs {
+    static constexpr int kPairs = kGZ / 2 + 1, kItems = kGRows * kPairs;
+    static constexpr int kIt = (kItems + kGThreads - 1) / kGThreads;
+    uint64_t p0[kIt], p1[kIt], p2[kIt];
+    __device__ __forceinline__ void load(const uint16_t* __restrict__ src, const GTile& t, int n) {
+#pragma unroll
+        for (int k = 0; k < kIt; ++k) {
+            const int i = int(threadIdx.x) + k * kGThreads;
+            p0[k] = p1[k] = p2[k] = 0ull;
+            if (i >= kItems) continue;
+            const int row = i / kPairs, pair = i - row * kPairs;
+            const int x = t.x0 + row / kGBY - 1, y = t.y0 + row % kGBY - 1, z = t.z0 + 2 * pair - 1;
+            if (x > n || y > n) continue;
+            const uint16_t* p = src + (int64_t(wrap_edge(x, n)) * n + wrap_edge(y, n)) * n * 4;
+            if (z <= n) p0[k] = *(const WDM_GAS uint64_t*)(p + int64_t(wrap_edge(z, n)) * 4);
+            if (z < n) p1[k] = *(const WDM_GAS uint64_t*)(p + int64_t(wrap_edge(z + 1, n)) * 4);
+            if (z + 1 < n && pair + 1 < kPairs)
+                p2[k] = *(const WDM_GAS uint64_t*)(p + int64_t(wrap_edge(z + 2, n)) * 4);
+        }
+    }
+    __device__ __forceinline__ void store(uint8_t* lds) const {
+#pragma unroll
+        for (int k = 0; k < kIt; ++k) {
+            const int i = int(threadIdx.x) + k * kGThreads;
+            if (i >= kItems) continue;
+            const int row = i / kPairs, pair = i - row * kPairs;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const uint32_t v0 = uint32_t(p0[k] >> (16 * c)) & 0xffffu,
+                               v1 = uint32_t(p1[k] >> (16 * c)) & 0xffffu,
+                               v2 = uint32_t(p2[k] >> (16 * c)) & 0xffffu;
+                uint8_t* p = lds + c * kGChanIn + row * kGRow + pair * 4;
+                if (pair + 1 < kPairs) {
+                    *reinterpret_cast<uint32_t*>(p) = v0 | (v1 << 16);
+                    *reinterpret_cast<uint32_t*>(p + 4 * kGChanIn) = v1 | (v2 << 16);
+                }
+                if (pair > 0) *reinterpret_cast<uint32_t*>(p + 8 * kGChanIn - 4) = v0 | (v1 << 16);
+            }
+        }
+    }
+};
+
+// Sum of the wavefronts' accumulators (NT 16 x 16 tiles each) in a fixed
+// order, written as part[tile][row][col].
+template <int NT>
+__device__ __forceinline__ void wgrad_write(float* lds, const f32x4* acc, float* dst) {
+    const int tid = int(threadIdx.x), lane = tid & 63, wave = tid >> 6;
+    const int col = lane & 15, kq = lane >> 4;
+    __syncthreads();   // the bricks are no longer read
+#pragma unroll
+    for (int round = 0; round < 2; ++round) {
+        if (wave / 4 == round) {
+            float* b = lds + (wave & 3) * (NT * 256);
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    float* e = b + t * 256 + (4 * kq + q) * 16 + col;
+                    *e = round ? *e + acc[t][q] : acc[t][q];
+                }
         }
         __syncthreads();
     }
-    float* dst = part + int64_t(blockIdx.x) * 16 * ROW;
-    for (int i = int(threadIdx.x); i < 16 * ROW; i += 256) gstr(dst, i, red[i]);
+    for (int i = tid; i < NT * 256; i += kGThreads)
+        gstr(dst, i, (lds[i] + lds[i + NT * 256]) + (lds[i + 2 * NT * 256] + lds[i + 3 * NT * 256]));
 }
 
-// Fixed-order sum of the work-group partials: out[i] = sum_b part[b][i].
-__global__ void k_sum_partials(const float* __restrict__ part, float* __restrict__ out,
-                               int nblocks, int len) {
-    const int i = int(blockIdx.x) * 256 + int(threadIdx.x);
-    if (i >= len) return;
+constexpr int kGTiles16 = 28;   // 27 taps and the bias (columns all equal)
+constexpr int kGTiles4 = 8;     // 7 groups of four taps and the bias
+
+// Hidden layer: 16 x 16 channels.  M = dz channel, N = act channel, one
+// accumulator tile per tap (112 registers a wavefront).  A lane reads ten
+// cells of an act row once and forms the three z taps from them; each
+// wavefront takes two of the tile's sixteen (x, y) rows.  Register prefetch of
+// the next tile, one LDS copy, one work-group of eight wavefronts per CU (the
+// partials' capacity).
+__global__ __launch_bounds__(kGThreads) void k_wgrad16(const uint16_t* __restrict__ dz,
+                                                       const uint16_t* __restrict__ act,
+                                                       float* __restrict__ part, int n) {
+    constexpr int kBrick = 16 * kGChanIn + 16 * kGChanOut;
+    constexpr int kSum = 4 * kGTiles16 * 256 * 4;
+    __shared__ __align__(16) uint8_t lds[kBrick > kSum ? kBrick : kSum];
+    uint8_t* la = lds;                     // act
+    uint8_t* lz = lds + 16 * kGChanIn;     // dz
+    const int lane = int(threadIdx.x) & 63, wave = int(threadIdx.x) >> 6;
+    const int ch = lane & 15, kq = lane >> 4;
+    const int tx = (n + kGX - 1) / kGX, ty = (n + kGY - 1) / kGY, tz = (n + kGZ - 1) / kGZ;
+    const int64_t ntiles = int64_t(tx) * ty * tz;
+    const bf16x8 ones = as_bf16x8(u32x4{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u});
+    f32x4 acc[kGTiles16];
+#pragma unroll
+    for (int t = 0; t < kGTiles16; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    HaloRegs ra;
+    OutRegs rz;
+    int64_t t = blockIdx.x;
+    if (t < ntiles) {
+        const GTile g(t, ty, tz);
+        ra.load(act, g, n);
+        rz.load(dz, g, n);
+    }
+    for (; t < ntiles; t += gridDim.x) {
+        const GTile g0(t, ty, tz);
+        ra.store(la);
+        rz.store(lz);
+        __syncthreads();
+        if (t + gridDim.x < ntiles) {
+            const GTile g(t + gridDim.x, ty, tz);
+            ra.load(act, g, n);
+            rz.load(dz, g, n);
+        }
+#pragma unroll 1
+        for (int rr = 0; rr < 2; ++rr) {
+            const int row = wave * 2 + rr, rx = row / kGY, ry = row % kGY;
+            if (g0.x0 + rx >= n || g0.y0 + ry >= n) continue;   // uniform over the wavefront
+            const bf16x8 a = lds_b128(lz + ch * kGChanOut + row * kGRow + kq * 16);
+            acc[27] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, ones, acc[27], 0, 0, 0);
+#pragma unroll
+            for (int d = 0; d < 9; ++d) {
+                const uint8_t* p =
+                    la + ch * kGChanIn + ((rx + d / 3) * kGBY + ry + d % 3) * kGRow + kq * 16;
+                const u32x4 w = *reinterpret_cast<const u32x4*>(p);
+                const uint32_t e = *reinterpret_cast<const uint32_t*>(p + 16);
+                const u32x4 w1 = {__builtin_amdgcn_alignbit(w[1], w[0], 16),
+                                  __builtin_amdgcn_alignbit(w[2], w[1], 16),
+                                  __builtin_amdgcn_alignbit(w[3], w[2], 16),
+                                  __builtin_amdgcn_alignbit(e, w[3], 16)};
+                const u32x4 w2 = {w[1], w[2], w[3], e};
+                acc[3 * d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, as_bf16x8(w), acc[3 * d], 0, 0, 0);
+                acc[3 * d + 1] =
+                    __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, as_bf16x8(w1), acc[3 * d + 1], 0, 0, 0);
+                acc[3 * d + 2] =
+                    __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, as_bf16x8(w2), acc[3 * d + 2], 0, 0, 0);
+            }
+        }
+        __syncthreads();   // the next tile's bricks overwrite these
+    }
+    wgrad_write<kGTiles16>(reinterpret_cast<float*>(lds), acc,
+                           part + int64_t(blockIdx.x) * (kGTiles16 * 256));
+}
+
+// The layers with a 4-channel side: `big` (16 channels) at the tile's cells,
+// `small` (4 channels) at the cell plus the tap.  M = big channel, N = (tap of
+// a group of four, small channel): 7 MFMAs per 32 cells where one per tap
+// would leave twelve of sixteen rows or columns empty.
+//   first layer: big = dz, small = act, the bias sums big;
+//   last layer: big = act, small = dz at p' = p - tap, so tap group entries are
+//   the mirrored taps; the bias sums the centre tap's small (BIAS_SMALL), its
+//   rows masked to the grid.
+template <bool BIAS_SMALL>
+__global__ __launch_bounds__(kGThreads) void k_wgrad4(const uint16_t* __restrict__ big,
+                                                      const uint16_t* __restrict__ small,
+                                                      float* __restrict__ part, int n) {
+    constexpr int kBrick = 12 * kGChanIn + 16 * kGChanOut;
+    constexpr int kSum = 4 * kGTiles4 * 256 * 4;
+    __shared__ __align__(16) uint8_t lds[kBrick > kSum ? kBrick : kSum];
+    uint8_t* ls = lds;                     // small, three shifted copies
+    uint8_t* lb = lds + 12 * kGChanIn;     // big
+    const int lane = int(threadIdx.x) & 63, wave = int(threadIdx.x) >> 6;
+    const int ch = lane & 15, kq = lane >> 4;
+    const int tx = (n + kGX - 1) / kGX, ty = (n + kGY - 1) / kGY, tz = (n + kGZ - 1) / kGZ;
+    const int64_t ntiles = int64_t(tx) * ty * tz;
+    // this lane's tap and channel of each group: LDS offset of its row
+    int off[7];
+#pragma unroll
+    for (int g = 0; g < 7; ++g) {
+        const int tap = min(4 * g + (ch >> 2), 26);   // the 28th entry is not used
+        off[g] = ((tap % 3) * 4 + (ch & 3)) * kGChanIn + ((tap / 9) * kGBY + (tap / 3) % 3) * kGRow +
+                 kq * 16;
+    }
+    f32x4 acc[kGTiles4];
+#pragma unroll
+    for (int t = 0; t < kGTiles4; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    Halo4Regs rs;
+    OutRegs rb;
+    int64_t t = blockIdx.x;
+    if (t < ntiles) {
+        const GTile g(t, ty, tz);
+        rs.load(small, g, n);
+        rb.load(big, g, n);
+    }
+    for (; t < ntiles; t += gridDim.x) {
+        const GTile g0(t, ty, tz);
+        rs.store(ls);
+        rb.store(lb);
+        __syncthreads();
+        if (t + gridDim.x < ntiles) {
+            const GTile g(t + gridDim.x, ty, tz);
+            rs.load(small, g, n);
+            rb.load(big, g, n);
+        }
+        // ones at the cells inside the grid along z
+        u32x4 ow;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int z = g0.z0 + 8 * kq + 2 * k;
+            ow[k] = (z < n ? 0x3f80u : 0u) | (z + 1 < n ? 0x3f800000u : 0u);
+        }
+        const bf16x8 ones = as_bf16x8(ow);
+#pragma unroll 1
+        for (int rr = 0; rr < 2; ++rr) {
+            const int row = wave * 2 + rr, rx = row / kGY, ry = row % kGY;
+            if (g0.x0 + rx >= n || g0.y0 + ry >= n) continue;   // uniform over the wavefront
+            const bf16x8 a = lds_b128(lb + ch * kGChanOut + row * kGRow + kq * 16);
+            const uint8_t* p = ls + (rx * kGBY + ry) * kGRow;
+#pragma unroll
+            for (int g = 0; g < 7; ++g) {
+                const bf16x8 b = lds_b128(p + off[g]);
+                acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc[g], 0, 0, 0);
+                if (BIAS_SMALL && g == 3)   // the centre tap is entry 1 of group 3
+                    acc[7] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, b, acc[7], 0, 0, 0);
+            }
+            if (!BIAS_SMALL) acc[7] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, ones, acc[7], 0, 0, 0);
+        }
+        __syncthreads();
+    }
+    wgrad_write<kGTiles4>(reinterpret_cast<float*>(lds), acc,
+                          part + int64_t(blockIdx.x) * (kGTiles4 * 256));
+}
+
+// Fixed-order sum of the work-groups' partials, straight into the parameter
+// layout w[co][ci][27], b[co].  64 entries per work-group, each by four lanes
+// over a quarter of the partials (one lane over all of them was 20 us a layer,
+// a chain of 256 dependent loads' latency).
+template <int LAYER>
+__global__ __launch_bounds__(256) void k_wgrad_sum(const float* __restrict__ part, int nblocks,
+                                                   float* __restrict__ gw, float* __restrict__ gb) {
+    constexpr int NT = LAYER == 1 ? kGTiles16 : kGTiles4;
+    constexpr int LEN = NT * 256;
+    __shared__ float red[4][64];
+    const int e = int(threadIdx.x) & 63, seg = int(threadIdx.x) >> 6;
+    const int i = int(blockIdx.x) * 64 + e;
+    const int per = (nblocks + 3) / 4, b0 = seg * per, b1 = min(nblocks, b0 + per);
     float s = 0.0f;
-    for (int b = 0; b < nblocks; ++b) s += gldr(part, int64_t(b) * len + i);
-    gstr(out, i, s);
+    int b = b0;
+    for (; b + 16 <= b1; b += 16) {
+        float v[16];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) v[k] = gldr(part, int64_t(b + k) * LEN + i);
+#pragma unroll
+        for (int k = 0; k < 16; ++k) s += v[k];
+    }
+    for (; b < b1; ++b) s += gldr(part, int64_t(b) * LEN + i);
+    red[seg][e] = s;
+    __syncthreads();
+    if (seg != 0) return;
+    s = (red[0][e] + red[1][e]) + (red[2][e] + red[3][e]);
+    const int tile = i >> 8, row = (i >> 4) & 15, col = i & 15;
+    if constexpr (LAYER == 1) {
+        if (tile < 27)
+            gstr(gw, (int64_t(row) * 16 + col) * 27 + tile, s);
+        else if (col == 0)
+            gstr(gb, row, s);
+    } else {
+        const int entry = 4 * tile + (col >> 2), c = col & 3;
+        if (tile < 7) {
+            if (LAYER == 0 && entry < 27 && c < 3) gstr(gw, (int64_t(row) * 3 + c) * 27 + entry, s);
+            if (LAYER == 2 && entry < 27 && c < 2)
+                gstr(gw, (int64_t(c) * 16 + row) * 27 + (26 - entry), s);
+        } else {
+            if (LAYER == 0 && col == 0) gstr(gb, row, s);
+            if (LAYER == 2 && row == 0 && (col >> 2) == 1 && c < 2) gstr(gb, c, s);
+        }
+    }
 }
 
 // ---- packing, loss, Adam ---------------------------------------------------
@@ -585,31 +883,9 @@ __global__ void k_set_scales(double* __restrict__ scal, double s_psi, double s_p
     gstr(scal, 5, s_out);
 }
 
-// Gradient sums [16][ROW] (k = tap * CPIN + c, bias at column KC*16) to the
-// FP32 parameter layout w[co][ci][27], b[co].
-__global__ void k_unpack_grads(const float* __restrict__ sum, float* __restrict__ gw,
-                               float* __restrict__ gb, int cin, int cout, int cpin, int row) {
-    const int i = int(blockIdx.x) * 256 + int(threadIdx.x);
-    const int nw = cout * cin * 27;
-    if (i < nw) {
-        const int co = i / (cin * 27), ci = (i / 27) % cin, tap = i % 27;
-        gstr(gw, i, gldr(sum, int64_t(co) * row + tap * cpin + ci));
-    } else if (i < nw + cout) {
-        const int co = i - nw;
-        gstr(gb, co, gldr(sum, int64_t(co) * row + (row - 1)));
-    }
-}
-
 // ---------------------------------------------------------------------------
 // host launchers
 // ---------------------------------------------------------------------------
-hipError_t net_unpack_grads(hipStream_t s, const float* sum, float* gw, float* gb, int cin,
-                            int cout, int cpin, int row) {
-    const int len = cout * cin * 27 + cout;
-    k_unpack_grads<<<(len + 255) / 256, 256, 0, s>>>(sum, gw, gb, cin, cout, cpin, row);
-    return hipGetLastError();
-}
-
 // Persistent grid of the convolution: one work-group per tile up to `per_cu`
 // per compute unit.  Eight at 4 input channels; three at 16, although their
 // 34.8 KB of LDS and 72-76 VGPRs would allow four: at 128^3 the forward pass
@@ -656,21 +932,30 @@ hipError_t conv_backward_data(hipStream_t s, int layer, const uint16_t* dz, cons
     return hipGetLastError();
 }
 
-int wgrad_row(int layer) { return ((27 * (layer == 0 ? 4 : 16) + 15) / 16) * 16 + 1; }
+// Floats of one work-group's weight-gradient partials, at most.
+int wgrad_part_floats() { return kGTiles16 * 256; }
 
+// Gradients of layer `layer`'s weights and biases into gw, gb: partials of at
+// most `max_blocks` work-groups in `part`, then their fixed-order sum.
 hipError_t conv_backward_weight(hipStream_t s, int layer, const uint16_t* dz,
-                                const uint16_t* act_in, float* part, int nblocks, float* out,
-                                int n) {
-    const int64_t cells = int64_t(n) * n * n;
-    const int64_t chunk = (cells + nblocks - 1) / nblocks;
-    if (layer == 0)
-        k_conv_wgrad<4, 16><<<nblocks, 256, 0, s>>>(dz, act_in, part, n, chunk);
-    else if (layer == 1)
-        k_conv_wgrad<16, 16><<<nblocks, 256, 0, s>>>(dz, act_in, part, n, chunk);
-    else
-        k_conv_wgrad<16, 4><<<nblocks, 256, 0, s>>>(dz, act_in, part, n, chunk);
-    const int len = 16 * wgrad_row(layer);
-    k_sum_partials<<<(len + 255) / 256, 256, 0, s>>>(part, out, nblocks, len);
+                                const uint16_t* act_in, float* part, int max_blocks, float* gw,
+                                float* gb, int n) {
+    const int64_t tiles = int64_t((n + kGX - 1) / kGX) * ((n + kGY - 1) / kGY) *
+                          ((n + kGZ - 1) / kGZ);
+    // one work-group per CU (LDS of the 16-channel kernel), two of the others;
+    // their partials are under a third of its
+    const int nb = int(tiles < max_blocks ? tiles : max_blocks);
+    const int nb2 = int(tiles < 2 * max_blocks ? tiles : 2 * max_blocks);
+    if (layer == 1) {
+        k_wgrad16<<<nb, kGThreads, 0, s>>>(dz, act_in, part, n);
+        k_wgrad_sum<1><<<kGTiles16 * 4, 256, 0, s>>>(part, nb, gw, gb);
+    } else if (layer == 0) {
+        k_wgrad4<false><<<nb2, kGThreads, 0, s>>>(dz, act_in, part, n);
+        k_wgrad_sum<0><<<kGTiles4 * 4, 256, 0, s>>>(part, nb2, gw, gb);
+    } else {
+        k_wgrad4<true><<<nb2, kGThreads, 0, s>>>(act_in, dz, part, n);
+        k_wgrad_sum<2><<<kGTiles4 * 4, 256, 0, s>>>(part, nb2, gw, gb);
+    }
     return hipGetLastError();
 }
 
