@@ -3,7 +3,7 @@
 Workload: the coupled halo -- 256^3 complex64 wave field (GRF with power
 exp(-k^2/k0^2), k0 = 16 * 2 pi / L, plus a soliton core) and 1e6 CIC-coupled
 Plummer baryon particles, dt = 0.2 dx^2 -- resident in HBM before timing.
-A step is one full kick-drift-kick step (all eight grid passes plus the
+A step is one full kick-drift-kick step (all grid passes plus the
 particle kick/drift/deposit; periodic particle re-sorts included).
 
 Prints one JSON line with the metric, a per-kernel roofline entry for the
@@ -35,12 +35,14 @@ BYTES_PER_CELL = {
     "z_potential_kick": 24, "y_fft_psi_fwd": 16, "x_kinetic": 16, "y_fft_psi_inv": 16,
     "z_density_r2c": 28, "y_fft_spec_fwd": 8, "x_green": 8, "y_fft_spec_inv": 8,
     "z_potential_close_kick": 24,
+    # the plane passes of the four-pass step
+    "xy_kinetic": 16, "xy_green": 8,
 }
 BYTES_PER_PARTICLE = {"particles_kick_drift_deposit": 48, "particles_close_kick": 36}
 # tuning-table slot of each grid pass (P1, P2/P4, P3, P5, P6/P8, P7)
 PASS_SLOT = {"z_potential_kick": 0, "z_potential_close_kick": 0, "y_fft_psi_fwd": 1,
              "y_fft_psi_inv": 1, "x_kinetic": 2, "z_density_r2c": 3, "y_fft_spec_fwd": 4,
-             "y_fft_spec_inv": 4, "x_green": 5}
+             "y_fft_spec_inv": 4, "x_green": 5, "xy_kinetic": 2, "xy_green": 5}
 
 
 def pass_variant(name, tuning):
@@ -51,8 +53,11 @@ def pass_variant(name, tuning):
 
 
 # grid passes that run while the particle kernel is in flight on its own stream
-OVERLAPS_PARTICLES = {"y_fft_psi_fwd", "x_kinetic", "y_fft_psi_inv"}
-STEP_BYTES_PER_CELL = 124
+OVERLAPS_PARTICLES = {"y_fft_psi_fwd", "x_kinetic", "y_fft_psi_inv", "xy_kinetic"}
+# algorithmic bytes per cell of a step: the four-pass form (all-default plan
+# tables on the grids that have it), or the eight-pass one
+STEP_BYTES_PER_CELL = 76
+STEP_BYTES_PER_CELL_EIGHT = 124
 STEP_BYTES_PER_PARTICLE = 48
 
 
@@ -239,7 +244,12 @@ def bench_ensemble(args):
     torch.cuda.synchronize()
     el = time.perf_counter() - t0
     ms = el * 1e3 / args.steps
-    step_bytes = STEP_BYTES_PER_CELL * cells + STEP_BYTES_PER_PARTICLE * parts
+    # classes whose tuned table is all default step in four passes
+    sizes = sorted({m.n for m in members})
+    per_cell = {n: STEP_BYTES_PER_CELL_EIGHT if any(tuning[6 * k:6 * k + 6]) else STEP_BYTES_PER_CELL
+                for k, n in enumerate(sizes)}
+    step_bytes = (sum(per_cell[m.n] * m.n ** 3 for m in members)
+                  + STEP_BYTES_PER_PARTICLE * parts)
     gbs = step_bytes / (ms * 1e-3) / 1e9
     out = {"metric": "aggregate grid cell-updates/s, 48-member mixed-size ensemble",
            "value": cells * args.steps / el, "unit": "cell-updates/s", "n_gpus": 1,
@@ -536,7 +546,10 @@ def main():
                      "sort_us": sort["avg_us"] if sort else None,
                      "sort_us_per_step": (sort["launches"] * sort["avg_us"] / args.steps
                                           if sort else 0.0)}
-    step_bytes = STEP_BYTES_PER_CELL * n3 + STEP_BYTES_PER_PARTICLE * wl.n_particles
+    # the passes the profiled region launched say which form the step took
+    per_cell = (STEP_BYTES_PER_CELL if "xy_kinetic" in per_kernel
+                else STEP_BYTES_PER_CELL_EIGHT)
+    step_bytes = per_cell * n3 + STEP_BYTES_PER_PARTICLE * wl.n_particles
     step_gbs = step_bytes / (ms_per_step * 1e-3) / 1e9
 
     learned_line = None

@@ -289,9 +289,11 @@ wdm_status wdm_use_graphs(wdm_plan* plan, int32_t enable);
  * wdm_set_state).  Ordering only affects speed and atomic summation order. */
 wdm_status wdm_set_sort_interval(wdm_plan* plan, int32_t interval);
 
-/* Autotuning of the step's FFT passes.  Each tunable pass (P1, P2/P4, P3, P5,
- * P6/P8, P7) of each size class chooses among up to four FFT plans: 0, the
- * default; 1, where the axis length allows (32, 64, 128, 256, 384, 512), twice
+/* Autotuning of the step's FFT passes.  A size class whose six choices are all
+ * 0 (the default) steps in four grid passes where the grid has them (periodic
+ * gravity, axes up to 256, large enough; else in eight, as with any other
+ * choice).  In the eight-pass step each tunable pass (P1, P2/P4, P3, P5, P6/P8,
+ * P7) of each size class chooses among up to four FFT plans: 0, the default; 1, where the axis length allows (32, 64, 128, 256, 384, 512), twice
  * the lanes per pencil and half the values per lane; 2, for the strided
  * passes (P2/P4, P3, P6/P8, P7) at axis lengths up to 256, the default radices
  * with twice the pencils per work-group (256-byte row segments for complex64,
@@ -303,7 +305,9 @@ wdm_status wdm_set_sort_interval(wdm_plan* plan, int32_t interval);
  * stream (a warm-up launch each, then `reps` rounds, reps in [1, 1000], timing
  * each plan once per round in rotating order, each launch between its own
  * events, on zeroed fields) and leaves the default unless another plan's
- * median is at least 2 % below the default's (then the fastest such plan).
+ * median is at least 2 % below the default's (then the fastest such plan); a
+ * table so chosen replaces the four-pass step only if its eight passes are 2 %
+ * faster as a whole.
  * It overwrites the members' states: call it before wdm_set_state, or set
  * every state again afterwards (wdm_step returns WDM_ESTATE until then).
  * Synchronises.  All plans give the same results up to rounding.

@@ -15,7 +15,8 @@ HERE = Path(__file__).resolve().parent
 CSRC = HERE / "csrc"
 LIB = HERE / "libwdm.so"
 OBJ = HERE / "_build"
-SOURCES = ["passes_z.hip", "passes_y.hip", "passes_x.hip", "particles.hip", "reduce.hip",
+SOURCES = ["passes_zy_c64.hip", "passes_zy_c128.hip", "passes_xy_c64.hip", "passes_xy_c128.hip",
+           "passes_z.hip", "passes_y.hip", "passes_x.hip", "particles.hip", "reduce.hip",
            "diag.hip", "isolated.hip", "corrector.hip", "spectral.hip", "fft_noalloc.hip", "capi.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

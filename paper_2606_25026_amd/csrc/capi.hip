@@ -90,7 +90,7 @@ struct Carver {
 };
 
 struct MemberLayout {
-    size_t psi, phi, rho_b, spec, nyq, kin, absorb, dt, results, watch, stab, rho_fx = 0;
+    size_t psi, phi, rho_b, spec, nyq, kin, xtab, absorb, dt, results, watch, stab, rho_fx = 0;
     size_t pad = 0, green = 0, ext = 0;   // vacuum boundary, external potential
     size_t p[7], a[7], key_a, key_b, idx_a, idx_b, hist;
 };
@@ -104,7 +104,7 @@ struct Layout {
 
 enum Kind : int {
     kKZPot = 0, kKParticles, kKYPsiF, kKXKin, kKYPsiI, kKZDens, kKYSpecF, kKXGreen, kKYSpecI,
-    kKClose, kKCloseParticles, kKSort, kKVacuum, kKPhiR2C, kKinds
+    kKClose, kKCloseParticles, kKSort, kKVacuum, kKPhiR2C, kKXYKin, kKXYGreen, kKinds
 };
 const char* kKindNames[kKinds] = {"z_potential_kick", "particles_kick_drift_deposit",
                                   "y_fft_psi_fwd",    "x_kinetic",
@@ -112,7 +112,8 @@ const char* kKindNames[kKinds] = {"z_potential_kick", "particles_kick_drift_depo
                                   "y_fft_spec_fwd",   "x_green",
                                   "y_fft_spec_inv",   "z_potential_close_kick",
                                   "particles_close_kick", "particle_sort",
-                                  "vacuum_poisson",   "z_phi_r2c"};
+                                  "vacuum_poisson",   "z_phi_r2c",
+                                  "xy_kinetic",       "xy_green"};
 
 bool valid_config(const wdm_config& c, std::string& why) {
     if (!axis_supported(c.nx) || !axis_supported(c.ny) || !axis_supported(c.nz)) {
@@ -217,6 +218,7 @@ bool make_layout(const wdm_config* mem, int n, Layout& L, std::string& why) {
         m.spec = c.take(int64_t(g.nx) * g.ny * (g.nz / 2) * cs);
         m.nyq = c.take(int64_t(g.nx) * g.ny * cs);
         m.kin = c.take((int64_t(g.nx) + int64_t(g.ny) * g.nz) * 16);
+        m.xtab = c.take(3 * int64_t(g.nx) * sizeof(double));
         m.absorb = c.take((int64_t(g.nx) + g.ny + g.nz) * sizeof(double));
         if (g.boundary == WDM_BOUNDARY_VACUUM) {
             m.pad = c.take(8 * cells * cs);
@@ -266,6 +268,15 @@ struct SizeClass {
     bool extended = false;  // some member has a self-interaction or absorbing boundary
     int64_t moving_np = 0;  // most particles of a member whose particles move
     bool vacuum = false;    // isolated Poisson solve (the class's members share the boundary)
+    // Whether the class steps in four passes: where the grid has them, the
+    // Poisson solve is periodic (the padded solve hands over a spectrum of its
+    // own form) and no other FFT plan was chosen for a pass.
+    bool four_passes() const {
+        if (vacuum || !split_supported(nx, ny, nz, count)) return false;
+        for (int v : var)
+            if (v != 0) return false;
+        return true;
+    }
 };
 
 struct Rec {
@@ -424,11 +435,26 @@ bool member_extended(const wdm_config& c) {
     return c.kappa != 0.0 || c.absorb_alpha != 0.0 || c.external_potential != 0;
 }
 
+// The size class of a device-table slot.
+const SizeClass& class_of(const wdm_plan* p, int dev) {
+    for (const auto& c : p->classes)
+        if (dev >= c.first && dev < c.first + c.count) return c;
+    return p->classes.front();
+}
+
 // Poisson solve of the density already deposited in rho_b plus |psi|^2
 // (psi in real space), ending with Phi written and psi untouched.
 hipError_t potential_from_state(wdm_plan* p, const Launch& L, const wdm_config& c,
                                 const double* rescale = nullptr) {
     hipError_t e;
+    if (class_of(p, L.first).four_passes()) {
+        if ((e = launch_zy_density(L, p->prec, c.nx, c.ny, c.nz, kDensDirect, -1, rescale)) !=
+            hipSuccess)
+            return e;
+        if ((e = launch_xy_green(L, p->prec, c.nx, c.ny, c.nz)) != hipSuccess) return e;
+        return launch_zy_kick(L, p->prec, c.nx, c.ny, c.nz, kZPhiOnly, kHalfKick,
+                              member_extended(c));
+    }
     if (c.boundary == WDM_BOUNDARY_VACUUM) {
         if (rescale != nullptr) return hipErrorInvalidValue;
         e = enqueue_vacuum_poisson(p, L.stream, L.first, L.count, c.nx, c.ny, c.nz,
@@ -555,6 +581,7 @@ wdm_status wdm_plan_create(const wdm_config* members, int32_t n_members, void* w
         m.spec_nyq = ws + ml.nyq;
         m.scratch = ws + L.scratch;
         m.kin = ws + ml.kin;
+        m.xtab = reinterpret_cast<double*>(ws + ml.xtab);
         m.absorb = reinterpret_cast<double*>(ws + ml.absorb);
         m.pad = c.boundary == WDM_BOUNDARY_VACUUM ? ws + ml.pad : nullptr;
         m.green = c.boundary == WDM_BOUNDARY_VACUUM ? ws + ml.green : nullptr;
@@ -694,7 +721,8 @@ wdm_status wdm_plan_create(const wdm_config* members, int32_t n_members, void* w
     }
     // absorbing factors of dt = 0 (all ones) until the first step sets dt
     for (const auto& c : p->classes)
-        if (launch_absorb_tables(Launch{p->stream, p->table, c.first, c.count}) != hipSuccess)
+        if (launch_absorb_tables(Launch{p->stream, p->table, c.first, c.count}) != hipSuccess ||
+            launch_kx2_tables(Launch{p->stream, p->table, c.first, c.count}) != hipSuccess)
             return cleanup(WDM_EDEVICE, "plan initialisation failed");
     // no external potential until one is set
     for (int d = 0; d < n_members; ++d) {
@@ -785,21 +813,28 @@ hipError_t enqueue_step(wdm_plan* p, hipStream_t s, hipStream_t aux, KickMode km
         const Launch L{s, p->table, c.first, c.count};
         const bool parts = c.moving_np > 0;
         const bool fork = parts && aux != nullptr;
+        const bool four = c.four_passes();
         if (!chk(timed(p, kKZPot, [&] {
-                return launch_z_potential_kick(L, prec, c.nx, c.ny, c.nz, kZKickFft, km,
-                                               c.var[kTzPot], c.extended);
+                return four ? launch_zy_kick(L, prec, c.nx, c.ny, c.nz, kZKickFft, km, c.extended)
+                            : launch_z_potential_kick(L, prec, c.nx, c.ny, c.nz, kZKickFft, km,
+                                                      c.var[kTzPot], c.extended);
             })))
             return e;
-        // The particle kernel overlaps the psi passes P2-P4 on the auxiliary
-        // stream.  A replayed graph keeps the branch enqueued first on the
-        // launching queue and P5 waits on the other one across queues, so the
-        // branch expected to take longer goes first: measured at 10^6
-        // particles, the particles at 128^3 (particles first 0.118 ms per step,
-        // P2 first 0.121 ms) and the psi passes at 256^3 (0.410 and 0.408 ms).
-        // The kernels take about 46 ns per 1000 particles and 8 ns per 1000
-        // cells for the three passes.
-        const bool parts_first = c.moving_np * 6 > int64_t(c.nx) * c.ny * c.nz;
+        // The particle kernel overlaps the psi passes between P1 and P5 (the
+        // kinetic plane pass, or P2-P4) on the auxiliary stream.  A replayed
+        // graph keeps the branch enqueued first on the launching queue and P5
+        // waits on the other one across queues, so the branch expected to take
+        // longer goes first (measured with P2-P4 at 10^6 particles: the
+        // particles at 128^3, 0.118 against 0.121 ms per step, the psi passes at
+        // 256^3, 0.408 against 0.410).  The kernels take about 46 ns per 1000
+        // particles, 4.2 ns per 1000 cells for the plane pass and 8 for P2-P4.
+        const bool parts_first =
+            c.moving_np * (four ? 11 : 6) > int64_t(c.nx) * c.ny * c.nz;
         auto psi_f = [&] {
+            if (four)
+                return chk(timed(p, kKXYKin, [&] {
+                    return launch_xy_kinetic(L, prec, c.nx, c.ny, c.nz);
+                }));
             return chk(timed(p, kKYPsiF, [&] {
                 return launch_y_fft_psi(L, prec, c.nx, c.ny, c.nz, false, c.var[kTyPsi]);
             }));
@@ -825,6 +860,17 @@ hipError_t enqueue_step(wdm_plan* p, hipStream_t s, hipStream_t aux, KickMode km
                            })))
                 return e;
             if (!psi_f()) return e;
+        }
+        if (four) {
+            if (fork && !chk(hipStreamWaitEvent(s, p->ev_join, 0))) return e;
+            if (!chk(timed(p, kKZDens, [&] {
+                    return launch_zy_density(L, prec, c.nx, c.ny, c.nz, kDensInvFft, keep_member);
+                })))
+                return e;
+            if (!chk(timed(p, kKXYGreen,
+                           [&] { return launch_xy_green(L, prec, c.nx, c.ny, c.nz); })))
+                return e;
+            continue;
         }
         if (!chk(timed(p, kKXKin, [&] {
                 return launch_x_kinetic(L, prec, c.nx, c.ny, c.nz, c.var[kTxKin]);
@@ -880,8 +926,11 @@ hipError_t enqueue_close(wdm_plan* p, hipStream_t s, int64_t n) {
     for (const auto& c : p->classes) {
         const Launch L{s, p->table, c.first, c.count};
         e = timed(p, kKClose, [&] {
-            return launch_z_potential_kick(L, p->prec, c.nx, c.ny, c.nz, kZKickOnly, kHalfKick, 0,
-                                           c.extended);
+            return c.four_passes()
+                       ? launch_zy_kick(L, p->prec, c.nx, c.ny, c.nz, kZKickOnly, kHalfKick,
+                                        c.extended)
+                       : launch_z_potential_kick(L, p->prec, c.nx, c.ny, c.nz, kZKickOnly,
+                                                 kHalfKick, 0, c.extended);
         });
         if (e == hipSuccess && c.moving_np > 0)
             e = timed(p, kKCloseParticles, [&] {
@@ -1160,6 +1209,19 @@ hipError_t tune_launch(wdm_plan* p, const Launch& L, const SizeClass& c, int slo
     }
 }
 
+// The grid passes of one merged step of the class, without particles.
+hipError_t tune_step(wdm_plan* p, const Launch& L, const SizeClass& c) {
+    hipError_t e;
+    if (c.four_passes()) {
+        if ((e = launch_zy_kick(L, p->prec, c.nx, c.ny, c.nz, kZKickFft, kFullKick, false)) != hipSuccess) return e;
+        if ((e = launch_xy_kinetic(L, p->prec, c.nx, c.ny, c.nz)) != hipSuccess) return e;
+        if ((e = launch_zy_density(L, p->prec, c.nx, c.ny, c.nz, kDensInvFft)) != hipSuccess) return e;
+        return launch_xy_green(L, p->prec, c.nx, c.ny, c.nz);
+    }
+    for (int slot : {kTzPot, kTyPsi, kTxKin, kTzDens, kTySpec, kTxGreen})
+        if ((e = tune_launch(p, L, c, slot, c.var[slot])) != hipSuccess) return e;
+    return hipSuccess;
+}
 
 }  // namespace
 
@@ -1188,8 +1250,15 @@ wdm_status wdm_set_tuning(wdm_plan* p, const int32_t* in, int32_t n) {
                                         : v == 2 ? "no wide-row plan for this pass and length"
                                                  : "no complex-exchange plan for this pass and length");
         }
-    for (size_t k = 0; k < p->classes.size(); ++k)
-        for (int j = 0; j < kTuneSlots; ++j) p->classes[k].var[j] = in[k * kTuneSlots + j];
+    for (size_t k = 0; k < p->classes.size(); ++k) {
+        SizeClass& c = p->classes[k];
+        const bool four = c.four_passes();
+        for (int j = 0; j < kTuneSlots; ++j) c.var[j] = in[k * kTuneSlots + j];
+        // a state's half spectrum follows the form of the passes that read it
+        if (c.four_passes() != four)
+            HIPCHK(launch_spec_form(Launch{p->stream, p->table, c.first, c.count}, p->prec, c.nx,
+                                    c.ny, c.nz, !four));
+    }
     drop_graphs(p);
     return WDM_OK;
 }
@@ -1266,6 +1335,31 @@ wdm_status wdm_autotune(wdm_plan* p, int32_t reps) {
             for (int i = 1; i < np; ++i)
                 if (med[i] < (1.0f - kTuneMargin) * med[0] && med[i] < med[best]) best = i;
             c.var[j] = plans[best];
+        }
+        // the chosen plans against the four-pass step, as whole sequences
+        SizeClass four = c;
+        for (int& v : four.var) v = 0;
+        if (e == hipSuccess && !c.four_passes() && four.four_passes()) {
+            const SizeClass* seq[2] = {&four, &c};
+            for (int i = 0; i < 2 && e == hipSuccess; ++i) e = tune_step(p, L, *seq[i]);
+            for (int r = 0; r < reps && e == hipSuccess; ++r)
+                for (int q = 0; q < 2 && e == hipSuccess; ++q) {
+                    const int i = (r + q) % 2;
+                    if ((e = hipEventRecord(evp(r, i, 0), p->stream)) != hipSuccess) break;
+                    if ((e = tune_step(p, L, *seq[i])) != hipSuccess) break;
+                    e = hipEventRecord(evp(r, i, 1), p->stream);
+                }
+            if (e == hipSuccess) e = hipStreamSynchronize(p->stream);
+            std::vector<float> t[2];
+            for (int r = 0; r < reps && e == hipSuccess; ++r)
+                for (int i = 0; i < 2 && e == hipSuccess; ++i) {
+                    float ms = 0.0f;
+                    e = hipEventElapsedTime(&ms, evp(r, i, 0), evp(r, i, 1));
+                    t[i].push_back(ms);
+                }
+            if (e != hipSuccess) break;
+            for (auto& x : t) std::sort(x.begin(), x.end());
+            if (t[1][reps / 2] >= (1.0f - kTuneMargin) * t[0][reps / 2]) c = four;
         }
     }
     release();

@@ -98,6 +98,26 @@ __device__ __forceinline__ void gst(cplx<T>* p, int64_t i, cplx<T> v) {
     ((__attribute__((address_space(1))) V*)p)[i] = V{v.re, v.im};
 }
 
+// The same through a base and a 32-bit byte offset per lane.  UNIFORM: the base
+// is the same for the whole wavefront and is kept in scalar registers (one
+// address register for all of a lane's accesses; otherwise the compiler forms
+// a 64-bit sum for each and keeps them from the loads to the stores).
+template <bool UNIFORM, typename T>
+__device__ __forceinline__ cplx<T> gld_at(const cplx<T>* base, uint32_t bytes) {
+    using V = typename Vec2<T>::type;
+    if constexpr (UNIFORM) asm("" : "+s"(base));
+    const __attribute__((address_space(1))) char* p = (const __attribute__((address_space(1))) char*)base;
+    const V v = *(const __attribute__((address_space(1))) V*)(p + bytes);
+    return {v.x, v.y};
+}
+template <bool UNIFORM, typename T>
+__device__ __forceinline__ void gst_at(cplx<T>* base, uint32_t bytes, cplx<T> v) {
+    using V = typename Vec2<T>::type;
+    if constexpr (UNIFORM) asm("" : "+s"(base));
+    __attribute__((address_space(1))) char* p = (__attribute__((address_space(1))) char*)base;
+    *(__attribute__((address_space(1))) V*)(p + bytes) = V{v.re, v.im};
+}
+
 // ---------------------------------------------------------------------------
 // compile-time helpers
 // ---------------------------------------------------------------------------

@@ -307,6 +307,11 @@ __device__ __forceinline__ void write_kinetic_table(const MemberDev& m, double d
         if (t < nx) {
             const double kx = (kTwoPi / m.lx) * signed_mode(int(t), nx);
             e = expi64(a * kx * kx);
+            cplx<double> x = e;   // as P3 forms it from its hi + lo pair
+            if constexpr (std::is_same<T, float>::value)
+                x = cplx<double>{double(float(e.re)) + double(float(e.re - double(float(e.re)))),
+                                 double(float(e.im)) + double(float(e.im - double(float(e.im))))};
+            gst(reinterpret_cast<cplx<double>*>(m.xtab + nx), t, x);
         } else {
             const int64_t u = t - nx;
             const double ky = (kTwoPi / m.ly) * signed_mode(int(u / nz), ny);
@@ -385,6 +390,71 @@ __device__ __forceinline__ void watch_max(unsigned long long* slots, int64_t n, 
     for (int s = 0; s < E; ++s)
         u = max(u, (unsigned long long)__double_as_longlong(x[s]) & 0x7fffffffffffffffull);
     watch_store(slots, n, __ockl_wfred_max_u64(u));
+}
+
+// 1 / x for normal x: hardware reciprocal refined by one Newton step in single
+// precision (within about one unit in the last place); FP64 division otherwise.
+__device__ __forceinline__ float recip(float x) {
+    const float r = __builtin_amdgcn_rcpf(x);
+    return fmaf(fmaf(-x, r, 1.0f), r, r);
+}
+__device__ __forceinline__ double recip(double x) { return 1.0 / x; }
+
+// Absorbing factors of one pencil for the extended kick: b_x b_y of the pencil
+// (returned) and the z factors staged in LDS, all loads issued with the
+// pass's other loads.  Ones when the member has no absorbing boundary.
+template <int NZ, int WG>
+__device__ __forceinline__ double load_absorb(double* bz, const MemberDev& m, int64_t q, bool ok) {
+    constexpr int R = (NZ + WG - 1) / WG;
+    if (m.absorb_alpha == 0.0) return 1.0;
+    const double* tz = m.absorb + m.nx + m.ny;
+    double r[R];
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+        const int i = int(threadIdx.x) + k * WG;
+        r[k] = (NZ % WG == 0 || i < NZ) ? gldr(tz, i) : 1.0;
+    }
+    double bxy = 1.0;
+    if (ok) {
+        const int64_t i = q / m.ny, j = q - i * m.ny;
+        bxy = gldr(m.absorb, i) * gldr(m.absorb, m.nx + j);
+    }
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+        const int i = int(threadIdx.x) + k * WG;
+        if (NZ % WG == 0 || i < NZ) bz[i] = r[k];
+    }
+    return bxy;
+}
+
+// Kick with the local self-interaction and the absorbing boundary (Sec. 2.2,
+// 3.1): the potential is V = Phi + kappa |psi|^2, taken from psi before the
+// kick (the kick keeps |psi|).  With `closes` the absorbing factor
+// B = b_x b_y b_z closes the step; in a merged kick (`full`) it falls between
+// the closing half kick of one step and the opening one of the next, whose
+// self-interaction then sees |B psi|^2:
+//   phase = -dt/eta (Phi + kappa |psi|^2 (1 + B^2) / 2),  psi <- B e^{i phase} psi.
+// `c` is -tau / eta of the kick as launched; `bxy` and `bz` come from
+// load_absorb.
+template <class FP, typename T, class LN>
+__device__ __forceinline__ void kick_general(cplx<T>* v, const cplx<T>* w, const T* phi,
+                                             const MemberDev& m, bool closes, bool full, double bxy,
+                                             const double* bz, double c, const LN& ln) {
+    const double kappa = m.kappa;
+    const bool mask = closes && m.absorb_alpha != 0.0;
+#pragma unroll
+    for (int s = 0; s < FP::E; ++s) {
+        const double re = double(w[s].re), im = double(w[s].im);
+        const double r2 = re * re + im * im;
+        const double b = mask ? bxy * bz[slot_elem<FP, FP::first()>(ln.t, s)] : 1.0;
+        const double pot = double(phi[s]) + kappa * r2 * (full ? 0.5 * (1.0 + b * b) : 1.0);
+        cplx<T> r = rotate(w[s], pot * c);
+        if (mask) {
+            r.re *= T(b);
+            r.im *= T(b);
+        }
+        v[s] = r;
+    }
 }
 
 // ---------------------------------------------------------------------------

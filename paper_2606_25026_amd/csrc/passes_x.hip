@@ -1,6 +1,6 @@
 // P3 and P7: the passes along x (kinetic phase, Green's function), and the
 // spectral kinetic energy.
-#include "passes_common.hpp"
+#include "passes_split.hpp"
 
 namespace wdm {
 
@@ -65,15 +65,6 @@ __global__ __launch_bounds__((wg_size<typename PlanFor<NX, V>::type, T>())) void
     pencil_fft<IP, true, T>(v, lds, tw, ln.t, ln);
     store_slots<IP, IP::last()>(v, psi, q, plane, ok, ln);
 }
-
-// 1 / x for normal x: hardware reciprocal refined by one Newton step in single
-// precision (within about one unit in the last place); FP64 division otherwise.
-__device__ __forceinline__ float recip(float x) {
-    const float r = __builtin_amdgcn_rcpf(x);
-    return fmaf(fmaf(-x, r, 1.0f), r, r);
-}
-__device__ __forceinline__ double recip(double x) { return 1.0 / x; }
-
 
 // P7: x forward, Green's function, x inverse, on the half spectrum and the
 // Nyquist plane.  |k|^2 is summed in FP64 from a per-work-group table of k_x^2;
@@ -318,6 +309,18 @@ hipError_t launch_kinetic_tables(const Launch& L, int prec, int64_t max_entries)
     return hipGetLastError();
 }
 
+__global__ __launch_bounds__(256) void k_kx2_tables(const MemberDev* __restrict__ mems, int first) {
+    const MemberDev& m = mems[first + blockIdx.x];
+    for (int i = int(threadIdx.x); i < m.nx; i += 256) {
+        const double kx = kTwoPi / m.lx * signed_mode(i, m.nx);
+        gstr(m.xtab, i, kx * kx);
+    }
+}
+hipError_t launch_kx2_tables(const Launch& L) {
+    k_kx2_tables<<<unsigned(L.count), 256, 0, L.stream>>>(L.members, L.first);
+    return hipGetLastError();
+}
+
 hipError_t launch_x_kinetic(const Launch& L, int prec, int nx, int ny, int nz, int variant) {
     return dispatch_n<XKin>(nx, L, prec, ny, nz, variant);
 }
@@ -326,6 +329,44 @@ hipError_t launch_x_green(const Launch& L, int prec, int nx, int ny, int nz, int
 }
 hipError_t launch_x_kinetic_energy(const Launch& L, int prec, int nx, int ny, int nz) {
     return dispatch_n<XKinE>(nx, L, prec, ny, nz);
+}
+
+// The four-pass step's entry points by precision.
+#define WDM_SPLIT_DECL(P)                                                                         \
+    hipError_t launch_zy_kick_##P(const Launch&, int, int, int, ZOp, KickMode, bool);             \
+    hipError_t launch_zy_density_##P(const Launch&, int, int, int, DensOp, int, const double*);   \
+    hipError_t launch_spec_form_##P(const Launch&, int, int, int, bool);                          \
+    hipError_t launch_xy_kinetic_##P(const Launch&, int, int, int);                               \
+    hipError_t launch_xy_green_##P(const Launch&, int, int, int);
+WDM_SPLIT_DECL(c64)
+WDM_SPLIT_DECL(c128)
+#undef WDM_SPLIT_DECL
+
+bool split_supported(int nx, int ny, int nz, int members) {
+    const int r1 = y_radix(ny);
+    if (r1 == 0 || !zrows_supported(nz, r1) || !plane_supported(nx, ny / r1)) return false;
+    const int r2 = ny / r1;
+    return int64_t(members) * r1 * (nz / plane_zc(r2, nz)) >= plane_min_tiles(nx, r2);
+}
+hipError_t launch_zy_kick(const Launch& L, int prec, int nx, int ny, int nz, ZOp op, KickMode kick,
+                          bool extended) {
+    return prec ? launch_zy_kick_c128(L, nx, ny, nz, op, kick, extended)
+                : launch_zy_kick_c64(L, nx, ny, nz, op, kick, extended);
+}
+hipError_t launch_zy_density(const Launch& L, int prec, int nx, int ny, int nz, DensOp op,
+                             int keep_member, const double* rescale) {
+    return prec ? launch_zy_density_c128(L, nx, ny, nz, op, keep_member, rescale)
+                : launch_zy_density_c64(L, nx, ny, nz, op, keep_member, rescale);
+}
+hipError_t launch_spec_form(const Launch& L, int prec, int nx, int ny, int nz, bool to_split) {
+    return prec ? launch_spec_form_c128(L, nx, ny, nz, to_split)
+                : launch_spec_form_c64(L, nx, ny, nz, to_split);
+}
+hipError_t launch_xy_kinetic(const Launch& L, int prec, int nx, int ny, int nz) {
+    return prec ? launch_xy_kinetic_c128(L, nx, ny, nz) : launch_xy_kinetic_c64(L, nx, ny, nz);
+}
+hipError_t launch_xy_green(const Launch& L, int prec, int nx, int ny, int nz) {
+    return prec ? launch_xy_green_c128(L, nx, ny, nz) : launch_xy_green_c64(L, nx, ny, nz);
 }
 
 }  // namespace wdm

@@ -3,63 +3,6 @@
 
 namespace wdm {
 
-// Absorbing factors of one pencil for the extended kick: b_x b_y of the pencil
-// (returned) and the z factors staged in LDS, all loads issued with the
-// pass's other loads.  Ones when the member has no absorbing boundary.
-template <int NZ, int WG>
-__device__ __forceinline__ double load_absorb(double* bz, const MemberDev& m, int64_t q, bool ok) {
-    constexpr int R = (NZ + WG - 1) / WG;
-    if (m.absorb_alpha == 0.0) return 1.0;
-    const double* tz = m.absorb + m.nx + m.ny;
-    double r[R];
-#pragma unroll
-    for (int k = 0; k < R; ++k) {
-        const int i = int(threadIdx.x) + k * WG;
-        r[k] = (NZ % WG == 0 || i < NZ) ? gldr(tz, i) : 1.0;
-    }
-    double bxy = 1.0;
-    if (ok) {
-        const int64_t i = q / m.ny, j = q - i * m.ny;
-        bxy = gldr(m.absorb, i) * gldr(m.absorb, m.nx + j);
-    }
-#pragma unroll
-    for (int k = 0; k < R; ++k) {
-        const int i = int(threadIdx.x) + k * WG;
-        if (NZ % WG == 0 || i < NZ) bz[i] = r[k];
-    }
-    return bxy;
-}
-
-// Kick with the local self-interaction and the absorbing boundary (Sec. 2.2,
-// 3.1): the potential is V = Phi + kappa |psi|^2, taken from psi before the
-// kick (the kick keeps |psi|).  With MASK the absorbing factor
-// B = b_x b_y b_z closes the step; in a merged kick (FULL) it falls between
-// the closing half kick of one step and the opening one of the next, whose
-// self-interaction then sees |B psi|^2:
-//   phase = -dt/eta (Phi + kappa |psi|^2 (1 + B^2) / 2),  psi <- B e^{i phase} psi.
-// `c` is -tau / eta of the kick as launched; `bxy` and `bz` come from
-// load_absorb.
-template <class FP, typename T, bool MASK, bool FULL, class LN>
-__device__ __forceinline__ void kick_general(cplx<T>* v, const cplx<T>* w, const T* phi,
-                                             const MemberDev& m, double bxy, const double* bz,
-                                             double c, const LN& ln) {
-    const double kappa = m.kappa;
-    const bool mask = MASK && m.absorb_alpha != 0.0;
-#pragma unroll
-    for (int s = 0; s < FP::E; ++s) {
-        const double re = double(w[s].re), im = double(w[s].im);
-        const double r2 = re * re + im * im;
-        const double b = mask ? bxy * bz[slot_elem<FP, FP::first()>(ln.t, s)] : 1.0;
-        const double pot = double(phi[s]) + kappa * r2 * (FULL ? 0.5 * (1.0 + b * b) : 1.0);
-        cplx<T> r = rotate(w[s], pot * c);
-        if (mask) {
-            r.re *= T(b);
-            r.im *= T(b);
-        }
-        v[s] = r;
-    }
-}
-
 // ===========================================================================
 // P1: potential from the half spectrum, kick, optional forward z-FFT.
 // ===========================================================================
@@ -169,7 +112,7 @@ __global__ __launch_bounds__((wg_size<typename PlanFor<NZ, V>::type, T>())) void
             for (int s = 0; s < FP::E; ++s) r2[s] = ok ? w[s].re * w[s].re + w[s].im * w[s].im : T(0);
             watch_max<FP::E>(m.watch + m.watch_n, m.watch_n, r2);
         }
-        kick_general<FP, T, MASK, KICK == kFullKick>(v, w, phi, m, bxy, bz, c, ln);
+        kick_general<FP, T>(v, w, phi, m, MASK, KICK == kFullKick, bxy, bz, c, ln);
     } else {
 #pragma unroll
         for (int s = 0; s < FP::E; ++s) v[s] = rotate(w[s], double(phi[s]) * c);

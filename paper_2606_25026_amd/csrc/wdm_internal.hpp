@@ -45,6 +45,9 @@ struct MemberDev {
     // [0, nx) e_x(k_x); [nx, nx + ny nz) e_yz(k_y, k_z) / N at q = iy nz + iz.
     // 16 bytes per entry: (hi, lo) complex64 pair, or one complex128.
     void* kin;
+    // x factors of the plane passes (FP64): [0, nx) k_x^2, written at plan
+    // creation; [nx, 3 nx) e_x(k_x) of the call's dt as complex128, written with kin
+    double* xtab;
     // absorbing-boundary factors of the step's dt, b_a = exp(-alpha dt g_a) at
     // the nodes: [0, nx) x, [nx, nx + ny) y, [nx + ny, nx + ny + nz) z (FP64)
     double* absorb;
@@ -141,6 +144,8 @@ hipError_t launch_y_fft_spec(const Launch& L, int prec, int nx, int ny, int nz, 
 // Kinetic factor tables e_x, e_yz / N of the dt in use (dt[0]) for every member
 // of the class; max_entries = the largest nx + ny nz of the class.
 hipError_t launch_kinetic_tables(const Launch& L, int prec, int64_t max_entries);
+// k_x^2 of every member of the class (xtab).
+hipError_t launch_kx2_tables(const Launch& L);
 // P3: x forward, kinetic phase exp(-i eta |k|^2 dt/2)/N, x inverse.
 hipError_t launch_x_kinetic(const Launch& L, int prec, int nx, int ny, int nz, int variant = 0);
 // P5: z inverse of psi (optional), rho = |psi|^2 + rho_b (rho_b cleared except
@@ -152,6 +157,20 @@ hipError_t launch_z_density(const Launch& L, int prec, int nx, int ny, int nz, D
                             const double* rescale = nullptr);
 // P7: x forward, Green's function -4 pi G / |k|^2 / N, x inverse (+ Nyquist plane).
 hipError_t launch_x_green(const Launch& L, int prec, int nx, int ny, int nz, int variant = 0);
+// ---- four-pass step (passes_split.hpp; passes_zy_*.hip, passes_xy_*.hip) ----
+// Whether a class of members of this grid takes it (P1, the kinetic plane pass,
+// P5 and the Green's plane pass in place of P1 - P8).
+bool split_supported(int nx, int ny, int nz, int members);
+// P1 (kZKickFft, kZKickOnly, kZPhiOnly), P5 (kDensInvFft, kDensDirect) and the
+// plane passes; the half spectrum is in the (y0, k1) form between them.
+hipError_t launch_zy_kick(const Launch& L, int prec, int nx, int ny, int nz, ZOp op, KickMode kick,
+                          bool extended);
+hipError_t launch_zy_density(const Launch& L, int prec, int nx, int ny, int nz, DensOp op,
+                             int keep_member = -1, const double* rescale = nullptr);
+hipError_t launch_xy_kinetic(const Launch& L, int prec, int nx, int ny, int nz);
+hipError_t launch_xy_green(const Launch& L, int prec, int nx, int ny, int nz);
+// The half spectrum (y in real space) to the (y0, k1) form, or back.
+hipError_t launch_spec_form(const Launch& L, int prec, int nx, int ny, int nz, bool to_split);
 // Plain 3D transforms between psi-shaped buffers: axis 0 = x, 1 = y, 2 = z.
 // `which` selects the member field: 0 = psi, 1 = scratch.
 hipError_t launch_axis_fft(const Launch& L, int prec, int nx, int ny, int nz, int axis,
