@@ -162,15 +162,49 @@ __device__ __forceinline__ void gatomic_add(unsigned long long* p, unsigned long
     atomicAdd(p, v);
 }
 
+// x of another lane of the wavefront by data-parallel primitive CTRL (0 where
+// there is none).
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp32(uint32_t x) {
+    return uint32_t(__builtin_amdgcn_update_dpp(0, int(x), CTRL, 0xf, 0xf, true));
+}
+template <int CTRL, typename A>
+__device__ __forceinline__ A dpp_from(A x) {
+    if constexpr (sizeof(A) == 4) {
+        uint32_t u;
+        __builtin_memcpy(&u, &x, 4);
+        u = dpp32<CTRL>(u);
+        __builtin_memcpy(&x, &u, 4);
+    } else {
+        uint32_t u[2];
+        __builtin_memcpy(u, &x, 8);
+        u[0] = dpp32<CTRL>(u[0]);
+        u[1] = dpp32<CTRL>(u[1]);
+        __builtin_memcpy(&x, u, 8);
+    }
+    return x;
+}
+template <int CTRL, typename A>
+__device__ __forceinline__ void run_step(A val[8], bool take) {
+#pragma unroll
+    for (int v = 0; v < 8; ++v) {
+        const A o = dpp_from<CTRL>(val[v]);
+        val[v] += take ? o : A(0);
+    }
+}
+
 // Per-run sums of the eight CIC contributions q * w of a wavefront: lanes
 // holding the same base cell (consecutive after the cell sort) form a run; on
-// return the run's first lane holds the run's sums in val[] and head = true.
-// All 64 lanes of the wavefront must call this together.
+// return the run's last lane holds the run's sums in val[] and true is
+// returned there.  A segmented inclusive scan by row shifts and row broadcasts,
+// register to register: the doubling by lane permutes it replaces is six rounds
+// of nine LDS round trips each.  All 64 lanes of the wavefront must call this
+// together.
 template <typename T, typename A>
 __device__ __forceinline__ bool wave_runs(const MemberDev& m, const CellW<T>& c, T q, bool act,
                                           A val[8], double scale) {
     const int lane = int(__lane_id());
-    const int64_t key = act ? (int64_t(c.i) * m.ny + c.j) * m.nz + c.k : -1 - lane;
+    const int key = act ? (c.i * m.ny + c.j) * m.nz + c.k : -1 - lane;   // cells < 2^27
 #pragma unroll
     for (int a = 0; a < 2; ++a)
 #pragma unroll
@@ -180,31 +214,27 @@ __device__ __forceinline__ bool wave_runs(const MemberDev& m, const CellW<T>& c,
                 val[a * 4 + b * 2 + d] =
                     act ? to_acc<A>(T(q * c.w[0][a] * c.w[1][b] * c.w[2][d]), scale) : A(0);
     // run heads: lanes whose key differs from the previous lane's
-    const int64_t prev = __shfl_up(key, 1);
+    const int prev = __shfl_up(key, 1);
     const bool head = lane == 0 || prev != key;
     const unsigned long long heads = __ballot(head);
     const unsigned long long upto = lane == 63 ? ~0ull : ((1ull << (lane + 1)) - 1ull);
-    const int seg = __popcll(heads & upto);
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const int oseg = __shfl_down(seg, off);
-        const bool take = (lane + off < 64) && (oseg == seg);
-#pragma unroll
-        for (int v = 0; v < 8; ++v) {
-            const A o = __shfl_down(val[v], off);
-            if (take) val[v] += o;
-        }
-    }
-    return head && act;
+    const int start = 63 - __clzll(heads & upto);   // the run's first lane
+    run_step<0x111>(val, lane - 1 >= start);        // row_shr:1, 2, 4, 8
+    run_step<0x112>(val, lane - 2 >= start);
+    run_step<0x114>(val, lane - 4 >= start);
+    run_step<0x118>(val, lane - 8 >= start);
+    // the sum up to the previous row's end, then up to lane 31
+    run_step<0x142>(val, (lane & 16) != 0 && start < (lane & 48));
+    run_step<0x143>(val, lane >= 32 && start < 32);
+    const bool tail = lane == 63 || ((heads >> (lane + 1)) & 1ull);
+    return tail && act;
 }
 
-// Deposit q * w into `grid` at the 8 nodes of cell c, one global atomic add
-// per node and wavefront run.
+// A run's sums into `grid` at the 8 nodes of its cell, one global atomic add per
+// node.
 template <typename T, typename A>
-__device__ __forceinline__ void deposit_wave(A* __restrict__ grid, const MemberDev& m,
-                                             const CellW<T>& c, T q, bool act, double scale) {
-    A val[8];
-    if (!wave_runs(m, c, q, act, val, scale)) return;
+__device__ __forceinline__ void deposit_run(A* __restrict__ grid, const MemberDev& m,
+                                            const CellW<T>& c, const A val[8]) {
     const int nx = m.nx, ny = m.ny, nz = m.nz;
     const int i1 = c.i + 1 == nx ? 0 : c.i + 1;
     const int j1 = c.j + 1 == ny ? 0 : c.j + 1;
@@ -231,51 +261,70 @@ constexpr int kParticleWG = 256;
 __device__ __forceinline__ int wave_min(int v) { return __ockl_wfred_min_i32(v); }
 __device__ __forceinline__ int wave_max(int v) { return __ockl_wfred_max_i32(v); }
 
+// LDS of a work-group's deposits: the node box and the wavefronts' cell bounds.
+// The box is zero between chunks (the flush clears what it reads).
+template <typename A>
+struct DepositLds {
+    A tile[tile_nodes<A>()];
+    int box[kParticleWG / 64][6];
+};
+template <typename A>
+__device__ __forceinline__ void deposit_init(DepositLds<A>& s) {
+    for (int t = int(threadIdx.x); t < tile_nodes<A>(); t += kParticleWG) s.tile[t] = A(0);
+}
+
 // Work-group deposit.  The particles of a work-group are consecutive in
 // Morton order, so their cells usually fill a small box: if that box (plus the
 // upper CIC node) holds at most tile_nodes<T>() nodes, the group accumulates
 // into LDS and issues one global atomic add per non-zero node; otherwise each
 // wavefront deposits its runs directly.  Every lane of the work-group must
-// call this (inactive lanes pass act = false).
+// call this (inactive lanes pass act = false).  Two barriers: after the
+// bounds, which also parts this chunk's sums from the last chunk's flush, and
+// after the sums, which parts the bounds' reads from the next chunk's writes.
 template <typename T, typename A>
-__device__ __forceinline__ void deposit_group(A* __restrict__ grid, const MemberDev& m,
-                                              const CellW<T>& c, T q, bool act, double scale) {
-    __shared__ A tile[tile_nodes<A>()];
-    __shared__ int box[6];
+__device__ __forceinline__ void deposit_group(DepositLds<A>& lds, A* __restrict__ grid,
+                                              const MemberDev& m, const CellW<T>& c, T q, bool act,
+                                              double scale) {
+    A* tile = lds.tile;
     const int tid = int(threadIdx.x);
     constexpr int kBig = 1 << 30;
     const int lo0 = wave_min(act ? c.i : kBig), lo1 = wave_min(act ? c.j : kBig),
               lo2 = wave_min(act ? c.k : kBig);
     const int hi0 = wave_max(act ? c.i : -1), hi1 = wave_max(act ? c.j : -1),
               hi2 = wave_max(act ? c.k : -1);
-    if (tid == 0) {
-        box[0] = box[1] = box[2] = kBig;
-        box[3] = box[4] = box[5] = -1;
-    }
-    __syncthreads();
     if (__lane_id() == 0) {
-        atomicMin(&box[0], lo0);
-        atomicMin(&box[1], lo1);
-        atomicMin(&box[2], lo2);
-        atomicMax(&box[3], hi0);
-        atomicMax(&box[4], hi1);
-        atomicMax(&box[5], hi2);
+        int* w = lds.box[tid >> 6];
+        w[0] = lo0;
+        w[1] = lo1;
+        w[2] = lo2;
+        w[3] = hi0;
+        w[4] = hi1;
+        w[5] = hi2;
     }
+    A val[8];
+    const bool tail = wave_runs(m, c, q, act, val, scale);
     __syncthreads();
-    if (box[3] < 0) return;  // no particle in the work-group (uniform)
-    const int i0 = box[0], j0 = box[1], k0 = box[2];
-    const int ex = box[3] - i0 + 2, ey = box[4] - j0 + 2, ez = box[5] - k0 + 2;
-    // extents are at most n + 1 <= 513 each, so the product fits in int64
-    const int64_t vol64 = int64_t(ex) * ey * ez;
+    int i0 = kBig, j0 = kBig, k0 = kBig, i1 = -1, j1 = -1, k1 = -1;
+#pragma unroll
+    for (int w = 0; w < kParticleWG / 64; ++w) {
+        i0 = min(i0, lds.box[w][0]);
+        j0 = min(j0, lds.box[w][1]);
+        k0 = min(k0, lds.box[w][2]);
+        i1 = max(i1, lds.box[w][3]);
+        j1 = max(j1, lds.box[w][4]);
+        k1 = max(k1, lds.box[w][5]);
+    }
+    const int ex = i1 - i0 + 2, ey = j1 - j0 + 2, ez = k1 - k0 + 2;
+    // extents are at most n + 1 <= 513 each, so the product fits in int64; a
+    // work-group without particles (uniform) has nothing to add
+    const int64_t vol64 = i1 < 0 ? 0 : int64_t(ex) * ey * ez;
     if (vol64 > tile_nodes<A>()) {
-        deposit_wave(grid, m, c, q, act, scale);
+        if (tail) deposit_run(grid, m, c, val);
+        __syncthreads();
         return;
     }
     const int vol = int(vol64);
-    for (int t = tid; t < vol; t += kParticleWG) tile[t] = A(0);
-    __syncthreads();
-    A val[8];
-    if (wave_runs(m, c, q, act, val, scale)) {
+    if (tail) {
         const int base = ((c.i - i0) * ey + (c.j - j0)) * ez + (c.k - k0);
 #pragma unroll
         for (int a = 0; a < 2; ++a)
@@ -286,6 +335,7 @@ __device__ __forceinline__ void deposit_group(A* __restrict__ grid, const Member
                     atomicAdd(&tile[base + (a * ey + b) * ez + d], val[a * 4 + b * 2 + d]);
     }
     __syncthreads();
+    if (vol == 0) return;
     const int nx = m.nx, ny = m.ny, nz = m.nz;
     const int eyz = ey * ez;
     // (ti, tj, tk) of node t = tid, advanced by the stride kParticleWG with
@@ -295,6 +345,7 @@ __device__ __forceinline__ void deposit_group(A* __restrict__ grid, const Member
               sk = kParticleWG - si * eyz - sj * ez;
     for (int t = tid; t < vol; t += kParticleWG) {
         const A v = tile[t];
+        tile[t] = A(0);
         const int ci = ti, cj = tj, ck = tk;
         tk += sk;
         tj += sj;
@@ -317,36 +368,47 @@ __device__ __forceinline__ void deposit_group(A* __restrict__ grid, const Member
     }
 }
 
-// mode 0: kick + drift + deposit into rho_b; 1: kick only; 2: deposit into
-// rho_b; 3: deposit into scratch (as a real grid).
-//
+// What a launch does with a member's particles (launch_particles' modes 0-3 in
+// terms of these).
+enum PartOp : int {
+    kPartAll = 0,      // kick, drift, deposit
+    kPartKick = 1,     // kick only
+    kPartDeposit = 2   // deposit only
+};
+constexpr int kToScratch = 1;    // deposit into scratch (a real grid), not rho_b
+constexpr int kSkipStatic = 2;   // leave members with static baryons alone
+
 // Persistent work-groups: at most `per_cu` per compute unit are launched and
-// each walks the member's 256-particle chunks with a grid stride.  Beside
-// longer y/x/y passes (the 256^3 step) four per CU leave them most of the
-// machine (0.4065 against 0.4103 ms per step with eight); where the particles
-// are the step's longer branch (10^6 particles on 128^3) eight per CU shorten
-// it (0.1146 against 0.1176 ms), and alone the kernel runs 44.5 against
-// 47 us at 256^3 + 10^6.
+// each walks the member's 256-particle chunks with a grid stride.  Beside the
+// longer psi passes of a 256^3 step four per CU leave them most of the machine;
+// where the particles are the step's longer branch (10^6 particles on 128^3) or
+// run alone, eight shorten them.  With the register scan of the runs and two
+// barriers a chunk instead of five the steps went 334.8 -> 331.5 us (256^3 +
+// 10^6), 94.6 -> 92.3 (128^3 + 10^6) and 116 -> 110 (128^3 complex128 + 10^5); a
+// move and a deposit kernel one after the other cost 8 us more than the one.
 constexpr int kGroupsPerCU = 4;
 
-// With S = m.substeps leapfrog sub-steps of h = dt / S (Sec. 3.2.2), mode 0
-// runs the opening (or merged) kick, then S drifts with a full kick of h in
-// the same potential between them; the closing half kick of h/2 is mode 1
-// after the step's Poisson solve.  Static baryons skip modes 0 and 1.
-template <typename T, bool DET>
+// With S = m.substeps leapfrog sub-steps of h = dt / S (Sec. 3.2.2), a step's
+// launch runs the opening (or merged) kick, then S drifts with a full kick of h
+// in the same potential between them; the closing half kick of h/2 is kPartKick
+// after the step's Poisson solve.  Static baryons are neither kicked nor moved.
+template <typename T, bool DET, int OP>
 __global__ __launch_bounds__(kParticleWG) void k_particles(const MemberDev* __restrict__ mems,
-                                                           int first, int mode, int kick) {
+                                                           int first, int flags, int kick) {
     const MemberDev& m = mems[first + blockIdx.y];
-    if (mode <= 1 && m.static_baryons) return;   // uniform over the work-group
+    if ((flags & kSkipStatic) && m.static_baryons) return;   // uniform over the work-group
     const double dt = gldr(m.dt, 0);
     const int S = m.substeps;
     const double h = dt / S;
+    using A = std::conditional_t<DET, unsigned long long, T>;
+    __shared__ DepositLds<std::conditional_t<OP == kPartKick, char, A>> lds;
+    if constexpr (OP != kPartKick) deposit_init(lds);   // the first chunk's barrier follows
     for (int64_t grp = blockIdx.x; grp * kParticleWG < m.np; grp += gridDim.x) {
         const int64_t i = grp * kParticleWG + threadIdx.x;
         const bool act = i < m.np;
         const int64_t ii = act ? i : 0;
         float x = gldr(m.px, ii), y = gldr(m.py, ii), z = gldr(m.pz, ii);
-        if (mode <= 1) {
+        if constexpr (OP != kPartDeposit) {
             float vx = gldr(m.vx, ii), vy = gldr(m.vy, ii), vz = gldr(m.vz, ii);
             float tau = float(kick == kFullKick ? h : 0.5 * h);
             for (int sub = 0;; ++sub) {
@@ -356,37 +418,35 @@ __global__ __launch_bounds__(kParticleWG) void k_particles(const MemberDev* __re
                 vx += g[0] * tau;
                 vy += g[1] * tau;
                 vz += g[2] * tau;
-                if (mode == 1) break;
+                if constexpr (OP == kPartKick) break;
                 x = wrap_pos(double(x) + double(vx) * h, m.lx, m.inv_lx);
                 y = wrap_pos(double(y) + double(vy) * h, m.ly, m.inv_ly);
                 z = wrap_pos(double(z) + double(vz) * h, m.lz, m.inv_lz);
                 if (sub + 1 == S) break;
                 tau = float(h);   // the two half kicks between sub-steps
             }
-            if (mode == 0) {
-                if (act) {
+            if (act) {
+                if constexpr (OP == kPartAll) {
                     gstr(m.px, i, x);
                     gstr(m.py, i, y);
                     gstr(m.pz, i, z);
                 }
-            }
-            if (act) {
                 gstr(m.vx, i, vx);
                 gstr(m.vy, i, vy);
                 gstr(m.vz, i, vz);
             }
-            if (mode == 1) continue;  // uniform; no barrier in this mode
         }
-        const T q = T(m.particle_mass * m.inv_dx * m.inv_dy * m.inv_dz);
-        const CellW<T> c = cic<T>(x, y, z, m);
-        if constexpr (DET) {
-            // fixed-point sums, turned into the real grid by k_fixed_to_real
-            deposit_group(m.rho_fx, m, c, q, act, m.fx_scale);
-        } else {
-            T* grid = static_cast<T*>(mode == 3 ? m.scratch : m.rho_b);
-            deposit_group(grid, m, c, q, act, 0.0);
+        if constexpr (OP != kPartKick) {
+            const T q = T(m.particle_mass * m.inv_dx * m.inv_dy * m.inv_dz);
+            const CellW<T> c = cic<T>(x, y, z, m);
+            if constexpr (DET) {
+                // fixed-point sums, turned into the real grid by k_fixed_to_real
+                deposit_group(lds, m.rho_fx, m, c, q, act, m.fx_scale);
+            } else {
+                T* grid = static_cast<T*>((flags & kToScratch) ? m.scratch : m.rho_b);
+                deposit_group(lds, grid, m, c, q, act, 0.0);
+            }
         }
-        __syncthreads();  // the next chunk reuses the group's LDS box and tile
     }
 }
 
@@ -430,26 +490,27 @@ hipError_t launch_particles(const Launch& L, int prec, int64_t max_np, int mode,
     if (max_np <= 0) return hipSuccess;
     if (per_cu <= 0) per_cu = kGroupsPerCU;
     const int64_t chunks = (max_np + kParticleWG - 1) / kParticleWG;
-    const int64_t cap = int64_t(per_cu) * device_cus();
-    dim3 grid(unsigned(chunks < cap ? chunks : cap), unsigned(L.count));
     const bool fx = det && mode != 1;   // mode 1 deposits nothing
-    if (prec) {
-        if (fx)
-            k_particles<double, true><<<grid, kParticleWG, 0, L.stream>>>(L.members, L.first,
-                                                                          mode, int(kick));
+    const int flags = (mode <= 1 ? kSkipStatic : 0) | (mode == 3 ? kToScratch : 0);
+    const int64_t cap = int64_t(per_cu) * device_cus();
+    const dim3 grid(unsigned(chunks < cap ? chunks : cap), unsigned(L.count));
+    auto go = [&](auto t, auto d) {
+        using T = decltype(t);
+        constexpr bool DET = decltype(d)::value;
+        if (mode == 1)
+            k_particles<T, false, kPartKick><<<grid, kParticleWG, 0, L.stream>>>(
+                L.members, L.first, flags, int(kick));
+        else if (mode == 0)
+            k_particles<T, DET, kPartAll><<<grid, kParticleWG, 0, L.stream>>>(
+                L.members, L.first, flags, int(kick));
         else
-            k_particles<double, false><<<grid, kParticleWG, 0, L.stream>>>(L.members, L.first,
-                                                                           mode, int(kick));
-    } else {
-        if (fx)
-            k_particles<float, true><<<grid, kParticleWG, 0, L.stream>>>(L.members, L.first,
-                                                                         mode, int(kick));
-        else
-            k_particles<float, false><<<grid, kParticleWG, 0, L.stream>>>(L.members, L.first,
-                                                                          mode, int(kick));
-    }
-    if (!fx) return hipGetLastError();
-    if (const hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+            k_particles<T, DET, kPartDeposit><<<grid, kParticleWG, 0, L.stream>>>(
+                L.members, L.first, flags, int(kick));
+        return hipGetLastError();
+    };
+    auto all = [&](auto t) { return fx ? go(t, std::true_type{}) : go(t, std::false_type{}); };
+    if (const hipError_t e = prec ? all(double()) : all(float()); e != hipSuccess) return e;
+    if (!fx) return hipSuccess;
     const dim3 cg(unsigned(4 * device_cus()), unsigned(L.count));
     const int to_scratch = mode == 3 ? 1 : 0, skip_static = mode == 0 ? 1 : 0;
     if (prec)
