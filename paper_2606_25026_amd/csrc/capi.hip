@@ -48,7 +48,6 @@ hipError_t net_set_scales(hipStream_t s, double* scal, double s_psi, double s_ph
 size_t net_moment_doubles();
 hipError_t launch_restrict_modes(hipStream_t s, const void* fine, void* coarse, int nf, int nc,
                                  int prec);
-hipError_t launch_contrast(const Launch& L, int prec, int64_t n);
 hipError_t launch_shells(const Launch& L, int prec, int nbins, double* part, double* out);
 hipError_t launch_distance(const Launch& L, int prec, const void* other, int64_t n, double* part,
                            double* out);
@@ -227,8 +226,8 @@ bool make_layout(const wdm_config* mem, int n, Layout& L, std::string& why) {
         if (g.external_potential) m.ext = c.take(cells * rs);
         m.dt = c.take(4 * sizeof(double));
         m.results = c.take(kRedFields * sizeof(double));
+        m.stab = c.take(2 * sizeof(double));   // dt, results, stab: one copy (read_scalars)
         m.watch = c.take(watch_words(g.nx, g.ny) * sizeof(unsigned long long));
-        m.stab = c.take(2 * sizeof(double));
         if (g.flags & WDM_DETERMINISTIC_DEPOSIT) m.rho_fx = c.take(cells * 8);
         const int64_t np = std::max<int64_t>(g.n_particles, 0);
         for (int a = 0; a < 7; ++a) m.p[a] = c.take(np * 4);
@@ -487,12 +486,25 @@ wdm_status stability_status(const wdm_config& c, const double stab[2]) {
 }
 
 // The stability checks of a member's steps so far (synchronises the stream).
-wdm_status check_stability(wdm_plan* p, int32_t member) {
-    double stab[2];
+// A member's time step, reductions and stability record behind the work queued
+// so far: one copy of the fields that the layout keeps next to each other, one
+// wait; the state's stability is judged on it.
+struct Scalars {
+    double dt[4], results[kRedFields], stab[2];
+};
+wdm_status read_scalars(wdm_plan* p, int32_t member, Scalars* out) {
     const MemberDev& m = p->host[p->dev_index[member]];
-    HIPCHK(hipMemcpyAsync(stab, m.stab, sizeof(stab), hipMemcpyDeviceToHost, p->stream));
+    const char* base = reinterpret_cast<const char*>(m.dt);
+    const size_t res = reinterpret_cast<const char*>(m.results) - base;
+    const size_t stab = reinterpret_cast<const char*>(m.stab) - base;
+    static_assert(sizeof(out->dt) <= kAlign && sizeof(out->results) <= kAlign, "layout");
+    char host[3 * kAlign];
+    HIPCHK(hipMemcpyAsync(host, base, stab + sizeof(out->stab), hipMemcpyDeviceToHost, p->stream));
     HIPCHK(hipStreamSynchronize(p->stream));
-    return stability_status(p->cfg[member], stab);
+    std::memcpy(out->dt, host, sizeof(out->dt));
+    std::memcpy(out->results, host + res, sizeof(out->results));
+    std::memcpy(out->stab, host + stab, sizeof(out->stab));
+    return stability_status(p->cfg[member], out->stab);
 }
 
 // Potential of a member's synchronised state (psi, particle positions): the
@@ -778,9 +790,8 @@ wdm_status wdm_set_state(wdm_plan* p, int32_t member, const void* psi, const flo
         HIPCHK(launch_particles(L, p->prec, c.n_particles, 2, kHalfKick, p->det, kPartsAlone));
     }
     HIPCHK(potential_from_state(p, L, c));
-    HIPCHK(launch_reduce_grid(L, p->prec, n, 0));
-    HIPCHK(launch_reduce_finish(L, 7, kRedBlocks, true));
-    HIPCHK(launch_reduce_finish(L, 8, kRedBlocks, true));
+    HIPCHK(launch_reduce_grid(L, p->prec, n, kSumState));
+    HIPCHK(launch_reduce_finish(L, 1u << 7 | 1u << 8, kRedBlocks));
     HIPCHK(launch_dt_auto(L, 0.9, kCKin));
     HIPCHK(launch_set_dt(L, t0, 3));
     p->has_state[member] = true;
@@ -1418,39 +1429,26 @@ wdm_status wdm_energy(wdm_plan* p, int32_t member, wdm_energy_t* out) {
     const MemberDev& m = p->host[p->dev_index[member]];
     const int64_t n = cells_of(c);
     const int prec = p->prec;
-    if (wdm_status st = check_stability(p, member)) return st;
-    // mass, max |Phi|, max |psi|^2 and sum |psi|^4
-    HIPCHK(launch_reduce_grid(L, prec, n, 0));
-    HIPCHK(launch_reduce_finish(L, 0, kRedBlocks, false));
-    HIPCHK(launch_reduce_finish(L, 7, kRedBlocks, true));
-    HIPCHK(launch_reduce_finish(L, 8, kRedBlocks, true));
-    HIPCHK(launch_reduce_finish(L, 9, kRedBlocks, false));
-    // potential energy with the deposited baryons
+    // mass, max |Phi|, max |psi|^2, sum |psi|^4 and the potential energy with the
+    // deposited baryons; the stored Phi carries the external potential, whose
+    // energy enters once
     HIPCHK(launch_zero(p->stream, m.scratch, size_t(n) * (prec ? 8 : 4)));
     if (c.n_particles > 0) HIPCHK(launch_particles(L, prec, c.n_particles, 3, kHalfKick, p->det));
-    HIPCHK(launch_reduce_grid(L, prec, n, 1));
-    HIPCHK(launch_reduce_finish(L, 2, kRedBlocks, false));
-    // the stored Phi carries the external potential; its energy enters once
-    if (m.ext) {
-        HIPCHK(launch_reduce_grid(L, prec, n, 2));
-        HIPCHK(launch_reduce_finish(L, 10, kRedBlocks, false));
-    }
-    // spectral kinetic energy: F_z, F_y into scratch, F_x fused with the sum
-    HIPCHK(hipMemcpyAsync(m.scratch, m.psi, size_t(n) * (prec ? 16 : 8), hipMemcpyDeviceToDevice,
-                          p->stream));
-    HIPCHK(launch_axis_fft(L, prec, c.nx, c.ny, c.nz, 2, false, 1));
-    HIPCHK(launch_axis_fft(L, prec, c.nx, c.ny, c.nz, 1, false, 1));
-    HIPCHK(launch_x_kinetic_energy(L, prec, c.nx, c.ny, c.nz));
-    HIPCHK(launch_reduce_finish(L, 1, int(axis_tiles(c.nx, int64_t(c.ny) * c.nz, prec)), false));
+    HIPCHK(launch_reduce_grid(L, prec, n, kSumState | kSumPot | (m.ext ? kSumExt : 0)));
+    unsigned fields = 1u << 0 | 1u << 2 | 1u << 7 | 1u << 8 | 1u << 9 | (m.ext ? 1u << 10 : 0u);
     if (c.n_particles > 0) {
         HIPCHK(launch_reduce_particles(L, c.n_particles));
-        for (int f = 3; f < 7; ++f) HIPCHK(launch_reduce_finish(L, f, kRedBlocks, false));
+        fields |= 1u << 3 | 1u << 4 | 1u << 5 | 1u << 6;
     }
-    double res[kRedFields], dts[4], stab[2];
-    HIPCHK(hipMemcpyAsync(res, m.results, sizeof(res), hipMemcpyDeviceToHost, p->stream));
-    HIPCHK(hipMemcpyAsync(dts, m.dt, sizeof(dts), hipMemcpyDeviceToHost, p->stream));
-    HIPCHK(hipMemcpyAsync(stab, m.stab, sizeof(stab), hipMemcpyDeviceToHost, p->stream));
-    HIPCHK(hipStreamSynchronize(p->stream));
+    HIPCHK(launch_reduce_finish(L, fields, kRedBlocks));
+    // spectral kinetic energy: F_z, F_y into scratch, F_x fused with the sum
+    HIPCHK(launch_z_fft_from(L, prec, c.nx, c.ny, c.nz, kFromPsi));
+    HIPCHK(launch_axis_fft(L, prec, c.nx, c.ny, c.nz, 1, false, 1));
+    HIPCHK(launch_x_kinetic_energy(L, prec, c.nx, c.ny, c.nz));
+    HIPCHK(launch_reduce_finish(L, 1u << 1, int(axis_tiles(c.nx, int64_t(c.ny) * c.nz, prec))));
+    Scalars sc;
+    if (wdm_status st = read_scalars(p, member, &sc)) return st;
+    const double *res = sc.results, *dts = sc.dt, *stab = sc.stab;
     const double dv = (c.lx / c.nx) * (c.ly / c.ny) * (c.lz / c.nz);
     const double eta = c.hbar_over_m;
     wdm_energy_t r;
@@ -1513,9 +1511,8 @@ wdm_status wdm_diagnostics(wdm_plan* p, int32_t member, const int32_t* centre,
     const Launch L = one(p, member);
     const MemberDev& m = p->host[p->dev_index[member]];
     const int64_t n = cells_of(c);
-    if (wdm_status st = check_stability(p, member)) return st;
     HIPCHK(launch_diag_energies(L, p->prec, kRedBlocks));
-    for (int f = 0; f < 7; ++f) HIPCHK(launch_reduce_finish(L, f, kRedBlocks, false));
+    HIPCHK(launch_reduce_finish(L, 0x7fu, kRedBlocks));
     const double dx = c.lx / c.nx;
     const bool cubic = dx == c.ly / c.ny && dx == c.lz / c.nz;
     double radii[9];
@@ -1525,14 +1522,15 @@ wdm_status wdm_diagnostics(wdm_plan* p, int32_t member, const int32_t* centre,
     double* hist = static_cast<double*>(m.scratch);
     if (cubic) {
         if (nbins + 9 > n) return fail(WDM_EINVAL, "grid too small for the radial histogram");
-        HIPCHK(launch_mass_radii(L, p->prec, n, cen, dx, hist, nbins, hist + nbins));
+        HIPCHK(launch_mass_radii(L, p->prec, c.nx, c.ny, cen, dx, hist, nbins, m.partials,
+                                 hist + nbins));
     }
-    double res[kRedFields];
-    HIPCHK(hipMemcpyAsync(res, m.results, sizeof(res), hipMemcpyDeviceToHost, p->stream));
     if (cubic)
         HIPCHK(hipMemcpyAsync(radii, hist + nbins, sizeof(radii), hipMemcpyDeviceToHost,
                               p->stream));
-    HIPCHK(hipStreamSynchronize(p->stream));
+    Scalars sc;
+    if (wdm_status st = read_scalars(p, member, &sc)) return st;
+    const double* res = sc.results;
     const double dv = dx * (c.ly / c.ny) * (c.lz / c.nz);
     out->K = res[0] * dv;
     out->Q = res[1] * dv;
@@ -1540,7 +1538,10 @@ wdm_status wdm_diagnostics(wdm_plan* p, int32_t member, const int32_t* centre,
     out->virial = 2.0 * out->K + 2.0 * out->Q + out->V;
     for (int a = 0; a < 3; ++a) out->momentum[a] = res[3 + a] * dv;
     out->mass = res[6] * dv;
-    for (int f = 0; f < 9; ++f) out->radii[f] = cubic ? radii[f] : std::nan("");
+    for (int f = 0; f < 9; ++f) {
+        if (cubic && std::isinf(radii[f])) radii[f] = -1.0;   // no mass
+        out->radii[f] = cubic ? radii[f] : std::nan("");
+    }
     return WDM_OK;
 }
 
@@ -2061,10 +2062,10 @@ wdm_status wdm_power_spectrum(wdm_plan* p, int32_t member, int32_t nbins, double
     if (!p->has_state[member]) return fail(WDM_ESTATE, "no state set");
     const Launch L = one(p, member);
     const int64_t n = cells_of(c);
-    HIPCHK(launch_reduce_grid(L, p->prec, n, 0));
-    HIPCHK(launch_reduce_finish(L, 0, kRedBlocks, false));
-    HIPCHK(launch_contrast(L, p->prec, n));
-    for (int ax = 2; ax >= 0; --ax)
+    HIPCHK(launch_reduce_grid(L, p->prec, n, kSumMass));
+    HIPCHK(launch_reduce_finish(L, 1u << 0, kRedBlocks));
+    HIPCHK(launch_z_fft_from(L, p->prec, c.nx, c.ny, c.nz, kFromContrast));
+    for (int ax = 1; ax >= 0; --ax)
         HIPCHK(launch_axis_fft(L, p->prec, c.nx, c.ny, c.nz, ax, false, 1));
     double* part = reinterpret_cast<double*>(p->ws + p->layout.pk);
     double* res = part + shells_partial_doubles() - 2 * 1024;

@@ -164,8 +164,7 @@ hipError_t launch_tidal_correct(const Launch& L, int prec, int64_t ncells) {
         k_tidal_partials<float><<<kRedBlocks, kIsoThreads, 0, L.stream>>>(L.members, L.first,
                                                                           kRedBlocks);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    for (int a = 0; a < 3; ++a)
-        if ((e = launch_reduce_finish(L, a, kRedBlocks, false)) != hipSuccess) return e;
+    if ((e = launch_reduce_finish(L, 0x7u, kRedBlocks)) != hipSuccess) return e;
     if (prec)
         k_tidal_apply<double><<<iso_grid(ncells), kIsoThreads, 0, L.stream>>>(L.members, L.first);
     else

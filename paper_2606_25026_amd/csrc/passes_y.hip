@@ -76,6 +76,55 @@ __global__ __launch_bounds__((wg_size<typename PlanFor<N>::type, T>())) void k_a
     }
 }
 
+// Forward z transform into scratch of what SRC names (ZSource), the pencil plan
+// and its arithmetic those of k_axis_fft: the copy of psi and the array of the
+// contrast (16 and 24 bytes a cell more) are not written.
+template <int N, typename T, int SRC>
+__global__ __launch_bounds__((wg_size<typename PlanFor<N>::type, T>())) void k_z_fft_from(
+    const MemberDev* __restrict__ mems, int first) {
+    using FP = typename PlanFor<N>::type;
+    using LN = Lanes<FP, T, false>;
+    __shared__ T lds[lds_entries<FP, T, false>()];
+    __shared__ cplx<T> tw[tw_entries<T>(N)];
+    const MemberDev& m = mems[first + blockIdx.y];
+    load_twiddles<N, wg_size<FP, T>()>(tw, m.tw_z);
+    __syncthreads();
+    const LN ln;
+    const int64_t rows = int64_t(m.nx) * m.ny;
+    const int64_t q = int64_t(blockIdx.x) * LN::PP + ln.p;
+    const bool ok = q < rows;
+    const int64_t b = ok ? q * N : 0;
+    cplx<T> v[FP::E];
+    load_slots<FP, FP::first()>(v, static_cast<const cplx<T>*>(m.psi), b, 1, ok, ln);
+    if constexpr (SRC == kFromContrast) {
+        const double mean = gldr(m.results, 0) / double(rows * N);
+#pragma unroll
+        for (int s = 0; s < FP::E; ++s) {
+            const double r = double(v[s].re) * v[s].re + double(v[s].im) * v[s].im;
+            v[s] = cplx<T>{ok ? T(r / mean - 1.0) : T(0), T(0)};
+        }
+    }
+    pencil_fft<FP, false, T>(v, lds, tw, ln.t, ln);
+    store_slots<FP, FP::last()>(v, static_cast<cplx<T>*>(m.scratch), b, 1, ok, ln);
+}
+
+template <int N>
+struct ZFftFrom {
+    template <typename T>
+    static hipError_t go(const Launch& L, int64_t pencils, int source) {
+        dim3 grid(unsigned(tiles<N, T>(pencils)), unsigned(L.count));
+        const auto b = block<N, T>();
+        if (source == kFromContrast)
+            k_z_fft_from<N, T, kFromContrast><<<grid, b, 0, L.stream>>>(L.members, L.first);
+        else
+            k_z_fft_from<N, T, kFromPsi><<<grid, b, 0, L.stream>>>(L.members, L.first);
+        return hipGetLastError();
+    }
+    static hipError_t run(const Launch& L, int prec, int64_t pencils, int source) {
+        return prec ? go<double>(L, pencils, source) : go<float>(L, pencils, source);
+    }
+};
+
 // Transforms of the vacuum solve's zero-padded grid (Sec. 3.2.1), run on the
 // padded member table (doubled lengths, psi = the padded grid).  Only the
 // quarter of the padded grid that can be non-zero before the x pass (x < nx,
@@ -258,6 +307,10 @@ hipError_t launch_axis_fft(const Launch& L, int prec, int nx, int ny, int nz, in
     const int64_t pencils = axis == 0 ? int64_t(ny) * nz
                                       : (axis == 1 ? int64_t(nx) * nz : int64_t(nx) * ny);
     return dispatch_n<AxisFft>(n, L, prec, pencils, axis, inverse, which);
+}
+
+hipError_t launch_z_fft_from(const Launch& L, int prec, int nx, int ny, int nz, int source) {
+    return dispatch_n<ZFftFrom>(nz, L, prec, int64_t(nx) * ny, source);
 }
 
 hipError_t launch_vac_fft(const Launch& L, int prec, int nx, int ny, int nz, int mode) {

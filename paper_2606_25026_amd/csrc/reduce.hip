@@ -41,49 +41,69 @@ __device__ __forceinline__ double block_max(double v, double* red) {
     return r;
 }
 
-// what 0: sum |psi|^2 -> field 0, max |Phi| -> field 7, max |psi|^2 -> field 8,
-//         sum |psi|^4 -> field 9
-// what 1: sum (|psi|^2 + scratch) Phi -> field 2 (scratch holds CIC rho_b)
-// what 2: sum (|psi|^2 + scratch) Phi_ext -> field 10
-template <typename T>
+// Sums and maxima over the grid chosen by WHAT (GridSum flags): kSumState
+// sum |psi|^2 -> field 0, max |Phi| -> 7, max |psi|^2 -> 8, sum |psi|^4 -> 9;
+// kSumPot sum (|psi|^2 + scratch) Phi -> field 2 (scratch holds CIC rho_b);
+// kSumExt sum (|psi|^2 + scratch) Phi_ext -> field 10; kSumMass sum |psi|^2 -> 0.
+// Streams its arrays once, four cells a lane in flight: 48 us for the 16 bytes a
+// cell of kSumState | kSumPot at 256^3, 5.6 TB/s (two passes of one cell a lane: 136).
+template <typename T, int WHAT>
 __global__ __launch_bounds__(kRedThreads) void k_reduce_grid(const MemberDev* __restrict__ mems,
-                                                             int first, int64_t n, int what) {
+                                                             int first, int64_t n) {
     __shared__ double red[kRedThreads];
     const MemberDev& m = mems[first];
     const int64_t chunk = (n + kRedBlocks - 1) / kRedBlocks;
     const int64_t b = int64_t(blockIdx.x) * chunk;
     const int64_t e = b + chunk < n ? b + chunk : n;
     const cplx<T>* psi = static_cast<const cplx<T>*>(m.psi);
-    const T* phi = static_cast<const T*>(what == 2 ? m.ext : m.phi);
+    const T* phi = static_cast<const T*>(m.phi);
     const T* rb = static_cast<const T*>(m.scratch);
-    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-    for (int64_t i = b + threadIdx.x; i < e; i += kRedThreads) {
-        const cplx<T> v = gld(psi, i);
+    const T* ext = static_cast<const T*>(m.ext);
+    constexpr bool STATE = (WHAT & kSumState) != 0, POT = (WHAT & kSumPot) != 0,
+                   EXT = (WHAT & kSumExt) != 0;
+    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0, s4 = 0.0, s5 = 0.0;
+    auto add = [&](cplx<T> v, T p, T r, T x) {
         const double re = double(v.re), im = double(v.im);
         const double rho = re * re + im * im;
-        if (what == 0) {
-            s0 += rho;
-            s1 = fmax(s1, fabs(double(gldr(phi, i))));
+        s0 += rho;
+        if constexpr (STATE) {
+            s1 = fmax(s1, fabs(double(p)));
             s2 = fmax(s2, rho);
             s3 += rho * rho;
-        } else {
-            s0 += (rho + double(gldr(rb, i))) * double(gldr(phi, i));
         }
-    }
-    const double t0 = block_sum<T>(s0, red);
-    if (what == 0) {
-        const double t1 = block_max(s1, red);
-        const double t2 = block_max(s2, red);
-        const double t3 = block_sum<T>(s3, red);
-        if (threadIdx.x == 0) {
-            m.partials[int64_t(blockIdx.x) * kRedFields + 0] = t0;
-            m.partials[int64_t(blockIdx.x) * kRedFields + 7] = t1;
-            m.partials[int64_t(blockIdx.x) * kRedFields + 8] = t2;
-            m.partials[int64_t(blockIdx.x) * kRedFields + 9] = t3;
+        if constexpr (POT) s4 += (rho + double(r)) * double(p);
+        if constexpr (EXT) s5 += (rho + double(r)) * double(x);
+    };
+    auto get_p = [&](int64_t i) { return STATE || POT ? gldr(phi, i) : T(0); };
+    auto get_r = [&](int64_t i) { return POT || EXT ? gldr(rb, i) : T(0); };
+    auto get_x = [&](int64_t i) { return EXT ? gldr(ext, i) : T(0); };
+    int64_t i = b + threadIdx.x;
+    for (; i + 3 * kRedThreads < e; i += 4 * kRedThreads) {
+        cplx<T> v[4];
+        T p[4], r[4], x[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            v[k] = gld(psi, i + k * kRedThreads);
+            p[k] = get_p(i + k * kRedThreads);
+            r[k] = get_r(i + k * kRedThreads);
+            x[k] = get_x(i + k * kRedThreads);
         }
-    } else if (threadIdx.x == 0) {
-        m.partials[int64_t(blockIdx.x) * kRedFields + (what == 2 ? 10 : 2)] = t0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) add(v[k], p[k], r[k], x[k]);
     }
+    for (; i < e; i += kRedThreads) add(gld(psi, i), get_p(i), get_r(i), get_x(i));
+    double* out = m.partials + int64_t(blockIdx.x) * kRedFields;
+    auto put = [&](int field, double t) {
+        if (threadIdx.x == 0) out[field] = t;
+    };
+    if constexpr (STATE || (WHAT & kSumMass)) put(0, block_sum<T>(s0, red));
+    if constexpr (STATE) {
+        put(7, block_max(s1, red));
+        put(8, block_max(s2, red));
+        put(9, block_sum<T>(s3, red));
+    }
+    if constexpr (POT) put(2, block_sum<T>(s4, red));
+    if constexpr (EXT) put(10, block_sum<T>(s5, red));
 }
 
 __global__ __launch_bounds__(kRedThreads) void k_reduce_particles(
@@ -108,11 +128,16 @@ __global__ __launch_bounds__(kRedThreads) void k_reduce_particles(
     }
 }
 
+// One work-group per field of `fields` (a bit mask): the partials' sum, or
+// their maximum for fields 7 and 8.
 __global__ __launch_bounds__(kRedThreads) void k_reduce_finish(const MemberDev* __restrict__ mems,
-                                                               int first, int field, int nblocks,
-                                                               int is_max) {
+                                                               int first, unsigned fields,
+                                                               int nblocks) {
     __shared__ double red[kRedThreads];
     const MemberDev& m = mems[first];
+    for (unsigned k = blockIdx.x; k > 0; --k) fields &= fields - 1;
+    const int field = __ffs(fields) - 1;
+    const bool is_max = field == 7 || field == 8;
     double s = 0.0;
     for (int i = int(threadIdx.x); i < nblocks; i += kRedThreads) {
         const double v = m.partials[int64_t(i) * kRedFields + field];
@@ -122,14 +147,23 @@ __global__ __launch_bounds__(kRedThreads) void k_reduce_finish(const MemberDev* 
     if (threadIdx.x == 0) m.results[field] = t;
 }
 
-hipError_t launch_reduce_grid(const Launch& L, int prec, int64_t ncells, int what) {
+template <int WHAT>
+static hipError_t reduce_grid(const Launch& L, int prec, int64_t n) {
     if (prec)
-        k_reduce_grid<double><<<kRedBlocks, kRedThreads, 0, L.stream>>>(L.members, L.first, ncells,
-                                                                        what);
+        k_reduce_grid<double, WHAT><<<kRedBlocks, kRedThreads, 0, L.stream>>>(L.members, L.first, n);
     else
-        k_reduce_grid<float><<<kRedBlocks, kRedThreads, 0, L.stream>>>(L.members, L.first, ncells,
-                                                                       what);
+        k_reduce_grid<float, WHAT><<<kRedBlocks, kRedThreads, 0, L.stream>>>(L.members, L.first, n);
     return hipGetLastError();
+}
+hipError_t launch_reduce_grid(const Launch& L, int prec, int64_t n, int what) {
+    switch (what) {
+        case kSumState: return reduce_grid<kSumState>(L, prec, n);
+        case kSumMass: return reduce_grid<kSumMass>(L, prec, n);
+        case kSumState | kSumPot: return reduce_grid<kSumState | kSumPot>(L, prec, n);
+        case kSumState | kSumPot | kSumExt:
+            return reduce_grid<kSumState | kSumPot | kSumExt>(L, prec, n);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 hipError_t launch_reduce_particles(const Launch& L, int64_t /*max_np*/) {
@@ -137,9 +171,9 @@ hipError_t launch_reduce_particles(const Launch& L, int64_t /*max_np*/) {
     return hipGetLastError();
 }
 
-hipError_t launch_reduce_finish(const Launch& L, int field, int nblocks, bool is_max) {
-    k_reduce_finish<<<1, kRedThreads, 0, L.stream>>>(L.members, L.first, field, nblocks,
-                                                     is_max ? 1 : 0);
+hipError_t launch_reduce_finish(const Launch& L, unsigned fields, int nblocks) {
+    k_reduce_finish<<<unsigned(__builtin_popcount(fields)), kRedThreads, 0, L.stream>>>(
+        L.members, L.first, fields, nblocks);
     return hipGetLastError();
 }
 

@@ -1,6 +1,8 @@
 // Spectral utilities of the learned-corrector workload: restriction of a fine
 // field to a coarser grid (keep the modes the coarse grid resolves, drop its
 // Nyquist plane) and the shell power spectrum of the density contrast.
+#include <algorithm>
+
 #include "wdm_internal.hpp"
 #include "fft_device.hpp"
 
@@ -46,35 +48,19 @@ hipError_t launch_restrict_modes(hipStream_t s, const void* fine, void* coarse, 
     return hipGetLastError();
 }
 
-// scratch = (|psi|^2 N / sum|psi|^2 - 1, 0); the FP64 sum is results[0].
-template <typename T>
-__global__ void k_contrast(const MemberDev* __restrict__ mems, int first, int64_t n) {
-    const MemberDev& m = mems[first];
-    const double mean = gldr(m.results, 0) / double(n);
-    const cplx<T>* psi = static_cast<const cplx<T>*>(m.psi);
-    cplx<T>* out = static_cast<cplx<T>*>(m.scratch);
-    for (int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x; i < n;
-         i += int64_t(gridDim.x) * 256) {
-        const cplx<T> v = gld(psi, i);
-        const double r = double(v.re) * v.re + double(v.im) * v.im;
-        gst(out, i, cplx<T>{T(r / mean - 1.0), T(0)});
-    }
-}
-
-hipError_t launch_contrast(const Launch& L, int prec, int64_t n) {
-    int64_t g = (n + 255) / 256;
-    if (g > 16384) g = 16384;
-    if (prec)
-        k_contrast<double><<<unsigned(g), 256, 0, L.stream>>>(L.members, L.first, n);
-    else
-        k_contrast<float><<<unsigned(g), 256, 0, L.stream>>>(L.members, L.first, n);
-    return hipGetLastError();
-}
-
 // Shell sums of |delta_k|^2 / N^2 over b = round(|m|) < nbins (cubic grid);
-// each block writes part[block][0..nbins) sums and [nbins..2 nbins) counts.
-constexpr int kPkBlocks = 64;
+// each work-group writes part[block][0..nbins) sums and [nbins..2 nbins) counts.
+// The modes (+-a, +-b, +-d) and (+-b, +-a, +-d) share a shell: a wavefront takes
+// pairs a >= b and a lane one d, which sums up to sixteen modes before its two
+// LDS additions.  Bound by its reads of the spectrum: 18 us at 256^3 (two
+// additions a mode over 64 work-groups: 565).
 constexpr int kPkMaxBins = 1024;
+constexpr int kPkDoubles = 64 * 2 * kPkMaxBins;   // partials of all work-groups
+constexpr int kPkMaxBlocks = 1024;
+
+static int shell_blocks(int nbins) {
+    return std::min(kPkMaxBlocks, kPkDoubles / (2 * nbins));
+}
 
 template <typename T>
 __global__ __launch_bounds__(256) void k_shells(const MemberDev* __restrict__ mems, int first,
@@ -87,19 +73,46 @@ __global__ __launch_bounds__(256) void k_shells(const MemberDev* __restrict__ me
         cnt[b] = 0ull;
     }
     __syncthreads();
-    const int n = m.nx;
-    const int64_t N = int64_t(n) * n * n;
-    const double norm = 1.0 / (double(N) * double(N));
+    const int n = m.nx, nh = n / 2 + 1;
+    const double N = double(n) * n * n;
+    const double norm = 1.0 / (N * N);
     const cplx<T>* f = static_cast<const cplx<T>*>(m.scratch);
-    for (int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x; i < N;
-         i += int64_t(gridDim.x) * 256) {
-        const double mx = smode(i / (int64_t(n) * n), n), my = smode((i / n) % n, n),
-                     mz = smode(i % n, n);
-        const int b = int(rint(sqrt(mx * mx + my * my + mz * mz)));
-        if (b >= nbins) continue;
-        const cplx<T> v = gld(f, i);
-        atomicAdd(&sum[b], (double(v.re) * v.re + double(v.im) * v.im) * norm);
-        atomicAdd(&cnt[b], 1ull);
+    const int lane = int(threadIdx.x) & 63;
+    auto twice = [n](int v) { return v != 0 && 2 * v != n ? 2 : 1; };
+    auto at = [n](int v, int sign) { return sign != 0 ? n - v : v; };
+    for (int pair = int(blockIdx.x) * 4 + (int(threadIdx.x) >> 6); pair < nh * nh;
+         pair += int(gridDim.x) * 4) {
+        const int a = pair / nh, b = pair - a * nh;
+        if (a < b) continue;
+        for (int d = lane; d < nh; d += 64) {
+            const int bin = int(rint(sqrt(double(a * a + b * b + d * d))));
+            if (bin >= nbins) continue;
+            // all sixteen loads in flight: an image that is no mode of its own
+            // reads its partner again and is left out of the sum
+            const int ia = twice(a) - 1, ib = twice(b) - 1, id = twice(d) - 1;
+            cplx<T> v[8][2];
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+                const int va = at(a, r & ia), vb = at(b, (r >> 1) & ib);
+                const cplx<T>* row = f + (int64_t(r < 4 ? va : vb) * n + (r < 4 ? vb : va)) * n;
+                v[r][0] = gld(row, d);
+                v[r][1] = gld(row, at(d, id));
+            }
+            double s = 0.0;
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+                const bool own = (r & 1) <= ia && ((r >> 1) & 1) <= ib && (r < 4 || a != b);
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    const cplx<T> w = v[r][k];
+                    const double p = double(w.re) * w.re + double(w.im) * w.im;
+                    s += own && k <= id ? p : 0.0;
+                }
+            }
+            atomicAdd(&sum[bin], s * norm);
+            atomicAdd(&cnt[bin], (unsigned long long)((a != b ? 2 : 1) * twice(a) * twice(b) *
+                                                      twice(d)));
+        }
     }
     __syncthreads();
     for (int b = int(threadIdx.x); b < nbins; b += 256) {
@@ -108,26 +121,35 @@ __global__ __launch_bounds__(256) void k_shells(const MemberDev* __restrict__ me
     }
 }
 
-__global__ void k_shells_finish(const double* __restrict__ part, double* __restrict__ out,
-                                int nbins, int nblocks) {
-    const int b = int(blockIdx.x) * 256 + int(threadIdx.x);
-    if (b >= 2 * nbins) return;
+// Sixteen of the 2 nbins columns a work-group, sixteen lanes to a column.
+__global__ __launch_bounds__(256) void k_shells_finish(const double* __restrict__ part,
+                                                       double* __restrict__ out, int nbins,
+                                                       int nblocks) {
+    __shared__ double red[16][17];
+    const int col = int(threadIdx.x) & 15, w = int(threadIdx.x) >> 4;
+    const int b = int(blockIdx.x) * 16 + col;
     double s = 0.0;
-    for (int k = 0; k < nblocks; ++k) s += gldr(part, int64_t(k) * 2 * nbins + b);
+    if (b < 2 * nbins)
+        for (int k = w; k < nblocks; k += 16) s += gldr(part, int64_t(k) * 2 * nbins + b);
+    red[w][col] = s;
+    __syncthreads();
+    if (w != 0 || b >= 2 * nbins) return;
+    for (int k = 1; k < 16; ++k) s += red[k][col];
     gstr(out, b, s);
 }
 
 hipError_t launch_shells(const Launch& L, int prec, int nbins, double* part, double* out) {
     if (nbins < 1 || nbins > kPkMaxBins) return hipErrorInvalidValue;
+    const int g = shell_blocks(nbins);
     if (prec)
-        k_shells<double><<<kPkBlocks, 256, 0, L.stream>>>(L.members, L.first, nbins, part);
+        k_shells<double><<<g, 256, 0, L.stream>>>(L.members, L.first, nbins, part);
     else
-        k_shells<float><<<kPkBlocks, 256, 0, L.stream>>>(L.members, L.first, nbins, part);
-    k_shells_finish<<<(2 * nbins + 255) / 256, 256, 0, L.stream>>>(part, out, nbins, kPkBlocks);
+        k_shells<float><<<g, 256, 0, L.stream>>>(L.members, L.first, nbins, part);
+    k_shells_finish<<<(2 * nbins + 15) / 16, 256, 0, L.stream>>>(part, out, nbins, g);
     return hipGetLastError();
 }
 
-size_t shells_partial_doubles() { return size_t(kPkBlocks) * 2 * kPkMaxBins + 2 * kPkMaxBins; }
+size_t shells_partial_doubles() { return size_t(kPkDoubles) + 2 * kPkMaxBins; }
 
 // FP64 partials of sum |psi - other|^2 and sum |other|^2 (the judge's field
 // distance) into part[2 b], part[2 b + 1] over a fixed grid of work-groups,

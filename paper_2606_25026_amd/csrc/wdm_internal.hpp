@@ -175,6 +175,10 @@ hipError_t launch_spec_form(const Launch& L, int prec, int nx, int ny, int nz, b
 // `which` selects the member field: 0 = psi, 1 = scratch.
 hipError_t launch_axis_fft(const Launch& L, int prec, int nx, int ny, int nz, int axis,
                            bool inverse, int which);
+// Forward z transform into scratch of psi (kFromPsi) or of its density contrast
+// |psi|^2 n / sum|psi|^2 - 1 (kFromContrast; the FP64 sum is results[0]).
+enum ZSource : int { kFromPsi = 0, kFromContrast = 1 };
+hipError_t launch_z_fft_from(const Launch& L, int prec, int nx, int ny, int nz, int source);
 // Transforms of the vacuum solve on the padded member table (nx, ny, nz the
 // padded lengths): mode 0 density rows of Phi -> padded rows, forward z;
 // 1 forward y (inputs y >= ny/2 zero); 2 inverse y (outputs y < ny/2 stored);
@@ -213,15 +217,19 @@ hipError_t launch_tidal_correct(const Launch& L, int prec, int64_t ncells);
 // over `nblocks` work-groups; finish each with launch_reduce_finish.
 hipError_t launch_diag_energies(const Launch& L, int prec, int nblocks);
 // Mass-fraction radii (10%, ..., 90%) around the node `centre` into out[0..8]
-// via a radial histogram hist[0..nbins) of squared node distances.
-hipError_t launch_mass_radii(const Launch& L, int prec, int64_t ncells, const int centre[3],
-                             double dx, double* hist, int64_t nbins, double* out);
+// (infinity where there is none) via a radial histogram hist[0..nbins) of squared
+// node distances; sums: radii_sums(nbins) doubles of scratch.
+inline int64_t radii_sums(int64_t nbins) { return (nbins + 1023) / 1024; }
+hipError_t launch_mass_radii(const Launch& L, int prec, int nx, int ny, const int centre[3],
+                             double dx, double* hist, int64_t nbins, double* sums, double* out);
 
 // ---- reductions and small kernels (reduce.hip) ----
 // fields of `results`: 0 mass, 1 e_kin, 2 sum rho Phi, 3 sum v^2, 4..6 sum v,
 // 7 max |Phi|, 8 max |psi|^2, 9 sum |psi|^4, 10 sum rho Phi_ext
+enum GridSum : int { kSumState = 1, kSumPot = 2, kSumExt = 4, kSumMass = 8 };
 hipError_t launch_reduce_grid(const Launch& L, int prec, int64_t ncells, int what);
-hipError_t launch_reduce_finish(const Launch& L, int field, int nblocks, bool is_max);
+// Finishes the fields of the bit mask `fields` from `nblocks` partials.
+hipError_t launch_reduce_finish(const Launch& L, unsigned fields, int nblocks);
 hipError_t launch_reduce_particles(const Launch& L, int64_t max_np);
 hipError_t launch_dt_auto(const Launch& L, double zeta, double c_kin);
 hipError_t launch_set_dt(const Launch& L, double dt, int mode);
