@@ -46,8 +46,6 @@ hipError_t net_moments(hipStream_t s, const float* x, const float* y, int64_t ce
 hipError_t net_fit_scales(hipStream_t s, const double* rows, double count, double* scal);
 hipError_t net_set_scales(hipStream_t s, double* scal, double s_psi, double s_phi, double s_out);
 size_t net_moment_doubles();
-hipError_t launch_restrict_modes(hipStream_t s, const void* fine, void* coarse, int nf, int nc,
-                                 int prec);
 hipError_t launch_shells(const Launch& L, int prec, int nbins, double* part, double* out);
 hipError_t launch_distance(const Launch& L, int prec, const void* other, int64_t n, double* part,
                            double* out);
@@ -2020,19 +2018,19 @@ wdm_status wdm_restrict(wdm_plan* fine, int32_t fmember, wdm_plan* coarse, int32
     if (fine->stream != coarse->stream) return fail(WDM_EINVAL, "plans must share a stream");
     if (!fine->has_state[fmember]) return fail(WDM_ESTATE, "no state set on the fine member");
     const int prec = fine->prec;
-    const MemberDev& mf = fine->host[fine->dev_index[fmember]];
     const MemberDev& mc = coarse->host[coarse->dev_index[cmember]];
     const Launch LF = one(fine, fmember), LC = one(coarse, cmember);
     const size_t cs = prec ? 16 : 8;
-    HIPCHK(hipMemcpyAsync(mf.scratch, mf.psi, size_t(cells_of(f)) * cs, hipMemcpyDeviceToDevice,
-                          fine->stream));
-    for (int ax = 2; ax >= 0; --ax)
-        HIPCHK(launch_axis_fft(LF, prec, f.nx, f.ny, f.nz, ax, false, 1));
-    HIPCHK(launch_restrict_modes(fine->stream, mf.scratch, mc.scratch, f.nx, c.nx, prec));
+    HIPCHK(launch_restrict_fft(LF, prec, f.nx, c.nx, mc.scratch));
+    // the last transform writes psi_out, or scratch and a copy if its address is
+    // no multiple of an element
+    const bool aligned = reinterpret_cast<uintptr_t>(psi_out) % cs == 0;
     for (int ax = 0; ax < 3; ++ax)
-        HIPCHK(launch_axis_fft(LC, prec, c.nx, c.ny, c.nz, ax, true, 1));
-    HIPCHK(hipMemcpyAsync(psi_out, mc.scratch, size_t(cells_of(c)) * cs, hipMemcpyDeviceToDevice,
-                          coarse->stream));
+        HIPCHK(launch_axis_fft(LC, prec, c.nx, c.ny, c.nz, ax, true, 1,
+                               aligned && ax == 2 ? psi_out : nullptr));
+    if (!aligned)
+        HIPCHK(hipMemcpyAsync(psi_out, mc.scratch, size_t(cells_of(c)) * cs,
+                              hipMemcpyDeviceToDevice, coarse->stream));
     return WDM_OK;
 }
 

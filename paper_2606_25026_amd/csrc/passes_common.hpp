@@ -342,10 +342,11 @@ struct Strides {
     }
 };
 
-// Plain transform of one batch of pencils.
+// Plain transform of one batch of pencils, in place or into `out`.
 template <class P, typename T, bool INV, bool STRIDED, typename LT>
 __device__ __forceinline__ void transform_tile(cplx<T>* data, const Strides& sd, int64_t tile,
-                                               LT* lds, const cplx<T>* tw) {
+                                               LT* lds, const cplx<T>* tw,
+                                               cplx<T>* out = nullptr) {
     using LN = Lanes<P, T, STRIDED>;
     const LN ln;
     const int64_t q = tile * LN::PP + ln.p;
@@ -354,7 +355,7 @@ __device__ __forceinline__ void transform_tile(cplx<T>* data, const Strides& sd,
     cplx<T> v[P::E];
     load_slots<P, P::first()>(v, data, b, sd.st, ok, ln);
     pencil_fft<P, INV, T>(v, lds, tw, ln.t, ln);
-    store_slots<P, P::last()>(v, data, b, sd.st, ok, ln);
+    store_slots<P, P::last()>(v, out != nullptr ? out : data, b, sd.st, ok, ln);
 }
 
 

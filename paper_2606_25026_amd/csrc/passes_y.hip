@@ -52,10 +52,11 @@ __global__ __launch_bounds__((wg_size<typename PlanFor<NY, V>::type, T>())) void
 }
 
 
-// Plain axis transform of psi or scratch (diagnostics, tests of the FFT).
+// Plain axis transform of psi or scratch (diagnostics, tests of the FFT), along
+// z into z_out if it is given.
 template <int N, typename T, bool INV, int AXIS>
 __global__ __launch_bounds__((wg_size<typename PlanFor<N>::type, T>())) void k_axis_fft(
-    const MemberDev* __restrict__ mems, int first, int which) {
+    const MemberDev* __restrict__ mems, int first, int which, cplx<T>* __restrict__ z_out) {
     using FP = typename PlanFor<N>::type;
     __shared__ T lds[lds_entries<FP, T, false>()];
     __shared__ cplx<T> tw[tw_entries<T>(N)];
@@ -66,7 +67,8 @@ __global__ __launch_bounds__((wg_size<typename PlanFor<N>::type, T>())) void k_a
     const int64_t nx = m.nx, ny = m.ny, nz = m.nz;
     if constexpr (AXIS == 2) {
         const Strides sd{nx * ny, 1, nz, 1};
-        transform_tile<FP, T, INV, false>(data, sd, blockIdx.x, lds, tw);
+        transform_tile<FP, T, INV, false>(data, sd, blockIdx.x, lds, tw,
+                                          z_out != nullptr ? z_out : data);
     } else if constexpr (AXIS == 1) {
         const Strides sd{nx * nz, nz, ny * nz, nz};
         transform_tile<FP, T, INV, true>(data, sd, blockIdx.x, lds, tw);
@@ -122,6 +124,70 @@ struct ZFftFrom {
     }
     static hipError_t run(const Launch& L, int prec, int64_t pencils, int source) {
         return prec ? go<double>(L, pencils, source) : go<float>(L, pencils, source);
+    }
+};
+
+// Forward transforms of psi that keep only the modes |m| < nc/2 of an axis (zero
+// on the coarse Nyquist plane), for the restriction of an N^3 grid: along z from
+// psi into scratch [N][N][nc], along y in place into its first nc rows, along x
+// into the coarse spectrum out [nc][nc][nc], times scale.  A pencil that ends in
+// dropped modes is never formed: at 256 -> 128 the three move 350 MB where full
+// transforms, the copy of psi and a gather of the kept modes moved 1.1 GB (195 ->
+// 67 us).
+template <int N, typename T, int AXIS>
+__global__ __launch_bounds__((wg_size<typename PlanFor<N>::type, T>())) void k_restrict_fft(
+    const MemberDev* __restrict__ mems, int first, int nc, cplx<T>* __restrict__ out, T scale) {
+    using FP = typename PlanFor<N>::type;
+    constexpr bool STRIDED = AXIS != 2;
+    using LN = Lanes<FP, T, STRIDED>;
+    __shared__ T lds[lds_entries<FP, T, false>()];
+    __shared__ cplx<T> tw[tw_entries<T>(N)];
+    const MemberDev& m = mems[first];
+    load_twiddles<N, wg_size<FP, T>()>(tw, AXIS == 0 ? m.tw_x : (AXIS == 1 ? m.tw_y : m.tw_z));
+    __syncthreads();
+    const LN ln;
+    const int64_t q = int64_t(blockIdx.x) * LN::PP + ln.p;
+    const int64_t plane = int64_t(N) * nc;
+    const bool ok = q < (AXIS == 2 ? int64_t(N) * N : AXIS == 1 ? plane : int64_t(nc) * nc);
+    const int64_t qq = ok ? q : 0;
+    const cplx<T>* in = static_cast<const cplx<T>*>(AXIS == 2 ? m.psi : m.scratch);
+    const int64_t b = AXIS == 2 ? qq * N : AXIS == 1 ? qq / nc * plane + qq % nc : qq;
+    const int64_t st = AXIS == 2 ? 1 : AXIS == 1 ? nc : plane;
+    cplx<T> v[FP::E];
+    load_slots<FP, FP::first()>(v, in, b, st, ok, ln);
+    pencil_fft<FP, false, T>(v, lds, tw, ln.t, ln);
+    if (!ok) return;
+    cplx<T>* to = AXIS == 0 ? out : static_cast<cplx<T>*>(m.scratch);
+    const int64_t ob = AXIS == 2 ? qq * nc : b, ost = AXIS == 0 ? int64_t(nc) * nc : st;
+#pragma unroll
+    for (int s = 0; s < FP::E; ++s) {
+        const int e = slot_elem<FP, FP::last()>(ln.t, s);
+        const int o = e < nc / 2 ? e : e - (N - nc);
+        if (e >= nc / 2 && o < nc / 2) continue;
+        cplx<T> w = AXIS == 0 ? cscale(v[s], scale) : v[s];
+        if (o == nc / 2) w = cplx<T>{T(0), T(0)};
+        gst(to, ob + o * ost, w);
+    }
+}
+
+template <int N>
+struct RestrictFft {
+    template <typename T>
+    static hipError_t go(const Launch& L, int nc, void* out) {
+        const auto b = block<N, T>();
+        const T scale = T(1.0 / (double(N) * N * N));
+        cplx<T>* o = static_cast<cplx<T>*>(out);
+        auto g = [](int64_t pencils) { return unsigned(tiles<N, T>(pencils)); };
+        k_restrict_fft<N, T, 2><<<g(int64_t(N) * N), b, 0, L.stream>>>(L.members, L.first, nc, o,
+                                                                       scale);
+        k_restrict_fft<N, T, 1><<<g(int64_t(N) * nc), b, 0, L.stream>>>(L.members, L.first, nc, o,
+                                                                        scale);
+        k_restrict_fft<N, T, 0><<<g(int64_t(nc) * nc), b, 0, L.stream>>>(L.members, L.first, nc, o,
+                                                                         scale);
+        return hipGetLastError();
+    }
+    static hipError_t run(const Launch& L, int prec, int nc, void* out) {
+        return prec ? go<double>(L, nc, out) : go<float>(L, nc, out);
     }
 };
 
@@ -272,24 +338,25 @@ struct YFft {
 template <int N>
 struct AxisFft {
     template <typename T, bool INV>
-    static hipError_t go2(const Launch& L, int64_t pencils, int axis, int which) {
+    static hipError_t go2(const Launch& L, int64_t pencils, int axis, int which, void* z_out) {
         dim3 grid(unsigned(tiles<N, T>(pencils)), unsigned(L.count));
         auto b = block<N, T>();
+        cplx<T>* zo = static_cast<cplx<T>*>(z_out);
         if (axis == 0)
-            k_axis_fft<N, T, INV, 0><<<grid, b, 0, L.stream>>>(L.members, L.first, which);
+            k_axis_fft<N, T, INV, 0><<<grid, b, 0, L.stream>>>(L.members, L.first, which, zo);
         else if (axis == 1)
-            k_axis_fft<N, T, INV, 1><<<grid, b, 0, L.stream>>>(L.members, L.first, which);
+            k_axis_fft<N, T, INV, 1><<<grid, b, 0, L.stream>>>(L.members, L.first, which, zo);
         else
-            k_axis_fft<N, T, INV, 2><<<grid, b, 0, L.stream>>>(L.members, L.first, which);
+            k_axis_fft<N, T, INV, 2><<<grid, b, 0, L.stream>>>(L.members, L.first, which, zo);
         return hipGetLastError();
     }
     static hipError_t run(const Launch& L, int prec, int64_t pencils, int axis, bool inv,
-                          int which) {
+                          int which, void* z_out) {
         if (prec)
-            return inv ? go2<double, true>(L, pencils, axis, which)
-                       : go2<double, false>(L, pencils, axis, which);
-        return inv ? go2<float, true>(L, pencils, axis, which)
-                   : go2<float, false>(L, pencils, axis, which);
+            return inv ? go2<double, true>(L, pencils, axis, which, z_out)
+                       : go2<double, false>(L, pencils, axis, which, z_out);
+        return inv ? go2<float, true>(L, pencils, axis, which, z_out)
+                   : go2<float, false>(L, pencils, axis, which, z_out);
     }
 };
 
@@ -302,11 +369,15 @@ hipError_t launch_y_fft_spec(const Launch& L, int prec, int nx, int ny, int nz, 
     return dispatch_n<YFft>(ny, L, prec, nx, nz, inverse, true, variant);
 }
 hipError_t launch_axis_fft(const Launch& L, int prec, int nx, int ny, int nz, int axis,
-                           bool inverse, int which) {
+                           bool inverse, int which, void* z_out) {
     const int n = axis == 0 ? nx : (axis == 1 ? ny : nz);
     const int64_t pencils = axis == 0 ? int64_t(ny) * nz
                                       : (axis == 1 ? int64_t(nx) * nz : int64_t(nx) * ny);
-    return dispatch_n<AxisFft>(n, L, prec, pencils, axis, inverse, which);
+    return dispatch_n<AxisFft>(n, L, prec, pencils, axis, inverse, which, z_out);
+}
+
+hipError_t launch_restrict_fft(const Launch& L, int prec, int nf, int nc, void* out) {
+    return dispatch_n<RestrictFft>(nf, L, prec, nc, out);
 }
 
 hipError_t launch_z_fft_from(const Launch& L, int prec, int nx, int ny, int nz, int source) {

@@ -1,52 +1,11 @@
-// Spectral utilities of the learned-corrector workload: restriction of a fine
-// field to a coarser grid (keep the modes the coarse grid resolves, drop its
-// Nyquist plane) and the shell power spectrum of the density contrast.
+// Spectral utilities of the learned-corrector workload: the shell power spectrum
+// of the density contrast and the distance between two fields.
 #include <algorithm>
 
 #include "wdm_internal.hpp"
 #include "fft_device.hpp"
 
 namespace wdm {
-
-__device__ __forceinline__ int smode(int64_t i, int n) { return int(i < n / 2 ? i : i - n); }
-
-// out[i,j,k] (coarse spectrum, nc^3) = in[m mod nf] * scale for |m_a| < nc/2,
-// 0 on the coarse Nyquist planes.
-template <typename T>
-__global__ void k_restrict_modes(const cplx<T>* __restrict__ fine, cplx<T>* __restrict__ coarse,
-                                 int nf, int nc, T scale) {
-    const int64_t nc3 = int64_t(nc) * nc * nc;
-    for (int64_t o = int64_t(blockIdx.x) * 256 + threadIdx.x; o < nc3;
-         o += int64_t(gridDim.x) * 256) {
-        const int mi = smode(o / (int64_t(nc) * nc), nc);
-        const int mj = smode((o / nc) % nc, nc);
-        const int mk = smode(o % nc, nc);
-        cplx<T> v{T(0), T(0)};
-        if (mi != -nc / 2 && mj != -nc / 2 && mk != -nc / 2) {
-            const int64_t fi = mi < 0 ? mi + nf : mi, fj = mj < 0 ? mj + nf : mj,
-                          fk = mk < 0 ? mk + nf : mk;
-            v = cscale(gld(fine, (fi * nf + fj) * nf + fk), scale);
-        }
-        gst(coarse, o, v);
-    }
-}
-
-hipError_t launch_restrict_modes(hipStream_t s, const void* fine, void* coarse, int nf, int nc,
-                                 int prec) {
-    const int64_t nc3 = int64_t(nc) * nc * nc;
-    int64_t g = (nc3 + 255) / 256;
-    if (g > 16384) g = 16384;
-    const double scale = 1.0 / (double(nf) * nf * nf);
-    if (prec)
-        k_restrict_modes<double><<<unsigned(g), 256, 0, s>>>(
-            static_cast<const cplx<double>*>(fine), static_cast<cplx<double>*>(coarse), nf, nc,
-            scale);
-    else
-        k_restrict_modes<float><<<unsigned(g), 256, 0, s>>>(
-            static_cast<const cplx<float>*>(fine), static_cast<cplx<float>*>(coarse), nf, nc,
-            float(scale));
-    return hipGetLastError();
-}
 
 // Shell sums of |delta_k|^2 / N^2 over b = round(|m|) < nbins (cubic grid);
 // each work-group writes part[block][0..nbins) sums and [nbins..2 nbins) counts.

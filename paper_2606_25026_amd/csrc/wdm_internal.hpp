@@ -172,9 +172,13 @@ hipError_t launch_xy_green(const Launch& L, int prec, int nx, int ny, int nz);
 // The half spectrum (y in real space) to the (y0, k1) form, or back.
 hipError_t launch_spec_form(const Launch& L, int prec, int nx, int ny, int nz, bool to_split);
 // Plain 3D transforms between psi-shaped buffers: axis 0 = x, 1 = y, 2 = z.
-// `which` selects the member field: 0 = psi, 1 = scratch.
+// `which` selects the member field: 0 = psi, 1 = scratch; z_out: where a z
+// transform's result goes instead (one member).
 hipError_t launch_axis_fft(const Launch& L, int prec, int nx, int ny, int nz, int axis,
-                           bool inverse, int which);
+                           bool inverse, int which, void* z_out = nullptr);
+// The modes of psi (nf^3) that an nc^3 grid resolves, / nf^3, into out [nc][nc][nc]
+// (zero on its Nyquist planes), through scratch; one member.
+hipError_t launch_restrict_fft(const Launch& L, int prec, int nf, int nc, void* out);
 // Forward z transform into scratch of psi (kFromPsi) or of its density contrast
 // |psi|^2 n / sum|psi|^2 - 1 (kFromContrast; the FP64 sum is results[0]).
 enum ZSource : int { kFromPsi = 0, kFromContrast = 1 };
