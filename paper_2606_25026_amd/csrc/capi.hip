@@ -783,8 +783,7 @@ wdm_status wdm_set_state(wdm_plan* p, int32_t member, const void* psi, const flo
     HIPCHK(launch_zero(p->stream, m.watch, (2 * m.watch_n + 2) * sizeof(unsigned long long)));
     HIPCHK(launch_zero(p->stream, m.stab, 2 * sizeof(double)));
     if (c.n_particles > 0) {
-        HIPCHK(launch_particle_upload(p->stream, m, pos, vel));
-        HIPCHK(launch_particle_sort(L, c.n_particles, c.nx, c.ny, c.nz));
+        HIPCHK(launch_particle_load(L, c.n_particles, c.nx, c.ny, c.nz, pos, vel));
         HIPCHK(launch_particles(L, p->prec, c.n_particles, 2, kHalfKick, p->det, kPartsAlone));
     }
     HIPCHK(potential_from_state(p, L, c));

@@ -525,18 +525,6 @@ hipError_t launch_particles(const Launch& L, int prec, int64_t max_np, int mode,
 // ---------------------------------------------------------------------------
 // upload / download (AoS [Np][3] <-> SoA, original order via id)
 // ---------------------------------------------------------------------------
-__global__ void k_upload(MemberDev m, const float* __restrict__ pos, const float* __restrict__ vel) {
-    const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
-    if (i >= m.np) return;
-    m.px[i] = wrap_pos(double(pos[3 * i + 0]), m.lx, m.inv_lx);
-    m.py[i] = wrap_pos(double(pos[3 * i + 1]), m.ly, m.inv_ly);
-    m.pz[i] = wrap_pos(double(pos[3 * i + 2]), m.lz, m.inv_lz);
-    m.vx[i] = vel[3 * i + 0];
-    m.vy[i] = vel[3 * i + 1];
-    m.vz[i] = vel[3 * i + 2];
-    m.id[i] = int32_t(i);
-}
-
 __global__ void k_unsort(MemberDev m, float* __restrict__ pos, float* __restrict__ vel) {
     const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
     if (i >= m.np) return;
@@ -553,13 +541,6 @@ __global__ void k_unsort(MemberDev m, float* __restrict__ pos, float* __restrict
     }
 }
 
-hipError_t launch_particle_upload(hipStream_t s, const MemberDev& m, const float* pos,
-                                  const float* vel) {
-    if (m.np <= 0) return hipSuccess;
-    k_upload<<<unsigned((m.np + 255) / 256), 256, 0, s>>>(m, pos, vel);
-    return hipGetLastError();
-}
-
 hipError_t launch_particle_unsort(hipStream_t s, const MemberDev& m, float* pos, float* vel) {
     if (m.np <= 0) return hipSuccess;
     k_unsort<<<unsigned((m.np + 255) / 256), 256, 0, s>>>(m, pos, vel);
@@ -569,7 +550,11 @@ hipError_t launch_particle_unsort(hipStream_t s, const MemberDev& m, float* pos,
 // ---------------------------------------------------------------------------
 // stable LSD radix sort of the particles by cell index (8-bit digits)
 // ---------------------------------------------------------------------------
-constexpr int kSortTile = 4096;   // keys per block: 256 lanes x 16 rounds
+// A work-group sorts 1024 keys, four a lane in registers (16 rounds of 256 with
+// three barriers each: a scatter of 10^6 keys took 20 us, 12 now; a histogram 11,
+// 7 now).
+constexpr int kSortRounds = 4;
+constexpr int kSortTile = 256 * kSortRounds;
 
 // Spread the low 10 bits of v to every third bit.
 __device__ __forceinline__ uint32_t spread3(uint32_t v) {
@@ -593,21 +578,65 @@ __device__ __forceinline__ int sort_tiles(int64_t np) {
 // Sort key: Morton (bit-interleaved) index of the particle's cell, so that
 // particles close in space are close in memory in all three directions and a
 // work-group's force gathers and deposits stay within a compact patch.
+__device__ __forceinline__ uint32_t sort_key(float x, float y, float z, const MemberDev& m) {
+    const CellW<float> c = cic<float>(x, y, z, m);
+    return (spread3(uint32_t(c.i)) << 2) | (spread3(uint32_t(c.j)) << 1) | spread3(uint32_t(c.k));
+}
+
 __global__ void k_make_keys(const MemberDev* __restrict__ mems, int first) {
     const MemberDev& m = mems[first + blockIdx.y];
     const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
     if (i >= m.np) return;
-    const CellW<float> c = cic<float>(m.px[i], m.py[i], m.pz[i], m);
-    m.key_a[i] = (spread3(uint32_t(c.i)) << 2) | (spread3(uint32_t(c.j)) << 1) |
-                 spread3(uint32_t(c.k));
+    m.key_a[i] = sort_key(m.px[i], m.py[i], m.pz[i], m);
     m.idx_a[i] = uint32_t(i);
 }
 
-// Lanes of the wavefront holding the same 8-bit digit (among `valid` lanes).
-__device__ __forceinline__ unsigned long long match_digit(uint32_t d, bool valid) {
+// Positions in the caller's order, wrapped into the box.
+struct Pos3 {
+    float x, y, z;
+};
+__device__ __forceinline__ Pos3 caller_pos(const float* __restrict__ pos, int64_t i,
+                                           const MemberDev& m) {
+    return {wrap_pos(double(pos[3 * i + 0]), m.lx, m.inv_lx),
+            wrap_pos(double(pos[3 * i + 1]), m.ly, m.inv_ly),
+            wrap_pos(double(pos[3 * i + 2]), m.lz, m.inv_lz)};
+}
+
+__global__ void k_load_keys(const MemberDev* __restrict__ mems, int first,
+                            const float* __restrict__ pos) {
+    const MemberDev& m = mems[first];
+    const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
+    if (i >= m.np) return;
+    const Pos3 p = caller_pos(pos, i, m);
+    m.key_a[i] = sort_key(p.x, p.y, p.z, m);
+    m.idx_a[i] = uint32_t(i);
+}
+
+// The caller's particles into the member's arrays in sorted order (the
+// permutation as in k_gather_sorted; passes < 0: the caller's order).  One gather
+// of two 12-byte rows a particle; the arrays of the member filled first, then
+// gathered from one by one and copied back took 91 + 30 us for 10^6, this 51.
+__global__ void k_load_sorted(const MemberDev* __restrict__ mems, int first, int passes,
+                              const float* __restrict__ pos, const float* __restrict__ vel) {
+    const MemberDev& m = mems[first];
+    const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
+    if (i >= m.np) return;
+    const int64_t s = passes < 0 ? i : int64_t(((passes & 1) ? m.idx_b : m.idx_a)[i]);
+    const Pos3 p = caller_pos(pos, s, m);
+    m.px[i] = p.x;
+    m.py[i] = p.y;
+    m.pz[i] = p.z;
+    m.vx[i] = vel[3 * s + 0];
+    m.vy[i] = vel[3 * s + 1];
+    m.vz[i] = vel[3 * s + 2];
+    m.id[i] = int32_t(s);
+}
+
+// Lanes of the wavefront holding the same digit of `bits` bits (among `valid`
+// lanes).
+__device__ __forceinline__ unsigned long long match_digit(uint32_t d, bool valid, int bits) {
     unsigned long long mask = __ballot(valid);
-#pragma unroll
-    for (int bit = 0; bit < 8; ++bit) {
+    for (int bit = 0; bit < bits; ++bit) {
         const bool on = (d >> bit) & 1u;
         const unsigned long long bb = __ballot(on);
         mask &= on ? bb : ~bb;
@@ -620,82 +649,91 @@ __device__ __forceinline__ unsigned long long match_digit(uint32_t d, bool valid
 // clustered), so equal digits are first counted across the wavefront and one
 // lane per digit adds the group size.
 __global__ __launch_bounds__(256) void k_radix_hist(const MemberDev* __restrict__ mems, int first,
-                                                    int pass) {
+                                                    int pass, int bits) {
     const MemberDev& m = mems[first + blockIdx.y];
     const int nb = sort_tiles(m.np);
     if (m.np <= 1 || int(blockIdx.x) >= nb) return;  // uniform per block
     const uint32_t* keys = (pass & 1) ? m.key_b : m.key_a;
-    const int shift = 8 * pass;
+    const int shift = bits * pass;
+    const uint32_t low = (1u << bits) - 1u;
     __shared__ uint32_t cnt[256];
     cnt[threadIdx.x] = 0;
+    uint32_t k[kSortRounds];
+    const int64_t b0 = int64_t(blockIdx.x) * kSortTile;
+#pragma unroll
+    for (int r = 0; r < kSortRounds; ++r) {
+        const int64_t i = b0 + r * 256 + threadIdx.x;
+        k[r] = i < m.np ? keys[i] : 0u;
+    }
     __syncthreads();
     const int lane = int(threadIdx.x) & 63;
     const unsigned long long lt = (1ull << lane) - 1ull;
-    const int64_t b0 = int64_t(blockIdx.x) * kSortTile;
-    for (int r = 0; r < kSortTile / 256; ++r) {
-        const int64_t i = b0 + r * 256 + threadIdx.x;
-        const bool valid = i < m.np;
-        const uint32_t d = valid ? (keys[i] >> shift) & 255u : 0u;
-        const unsigned long long mask = match_digit(d, valid);
-        if (valid && __popcll(mask & lt) == 0) atomicAdd(&cnt[d], uint32_t(__popcll(mask)));
+#pragma unroll
+    for (int r = 0; r < kSortRounds; ++r) {
+        const bool valid = b0 + r * 256 + int(threadIdx.x) < m.np;
+        const uint32_t d = (k[r] >> shift) & low;
+        const unsigned long long mask = match_digit(d, valid, bits);
+        if (valid && (mask & lt) == 0) atomicAdd(&cnt[d], uint32_t(__popcll(mask)));
     }
     __syncthreads();
     m.hist[int64_t(threadIdx.x) * nb + blockIdx.x] = cnt[threadIdx.x];
 }
 
-// Exclusive scan of the digit-major histogram hist[d * nb + b] in two small
-// kernels: each of 256 blocks scans one digit's column over the nb tile blocks
-// (and records the digit total after the histogram, at hist + 256 nb); one
-// block then scans the 256 totals, which k_radix_scatter adds as the digit
-// base.
+// Exclusive scan over a work-group of 256; `total` gets the sum.  Every lane
+// calls it, and a barrier lies between two uses of `s`.
+__device__ __forceinline__ uint32_t block_scan(uint32_t v, uint32_t* s, uint32_t* total) {
+    const int lane = int(threadIdx.x) & 63, wave = int(threadIdx.x) >> 6;
+    uint32_t x = v;
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t o = __shfl_up(x, off);
+        if (lane >= off) x += o;
+    }
+    if (lane == 63) s[wave] = x;
+    __syncthreads();
+    uint32_t before = 0, all = 0;
+    for (int w = 0; w < 4; ++w) {
+        if (w < wave) before += s[w];
+        all += s[w];
+    }
+    *total = all;
+    return before + x - v;
+}
+
+// Exclusive scan of the digit-major histogram hist[d * nb + b]: each of 256
+// blocks scans one digit's column over the nb tile blocks and records the digit
+// total after the histogram, at hist + 256 nb; k_radix_scatter scans the totals.
 __global__ __launch_bounds__(256) void k_scan_digit(const MemberDev* __restrict__ mems,
                                                     int first) {
     const MemberDev& m = mems[first + blockIdx.y];
     if (m.np <= 1) return;
     const int nb = sort_tiles(m.np);
-    __shared__ uint32_t s[256];
+    __shared__ uint32_t s[2][4];
     uint32_t* col = m.hist + int64_t(blockIdx.x) * nb;
     uint32_t carry = 0;
-    for (int b0 = 0; b0 < nb; b0 += 256) {
-        const int b = b0 + int(threadIdx.x);
-        const uint32_t v = b < nb ? col[b] : 0u;
-        s[threadIdx.x] = v;
-        __syncthreads();
-        for (int off = 1; off < 256; off <<= 1) {
-            const uint32_t t = int(threadIdx.x) >= off ? s[threadIdx.x - off] : 0u;
-            __syncthreads();
-            s[threadIdx.x] += t;
-            __syncthreads();
+    for (int b0 = 0, turn = 0; b0 < nb; b0 += 1024, turn ^= 1) {
+        const int b = b0 + 4 * int(threadIdx.x);
+        uint32_t v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = b + k < nb ? col[b + k] : 0u;
+        uint32_t total;
+        uint32_t x = carry + block_scan(v[0] + v[1] + v[2] + v[3], s[turn], &total);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if (b + k < nb) col[b + k] = x;
+            x += v[k];
         }
-        if (b < nb) col[b] = carry + s[threadIdx.x] - v;
-        carry += s[255];
-        __syncthreads();
+        carry += total;
     }
     if (threadIdx.x == 0) m.hist[int64_t(256) * nb + blockIdx.x] = carry;
 }
 
-__global__ __launch_bounds__(256) void k_scan_totals(const MemberDev* __restrict__ mems,
-                                                     int first) {
-    const MemberDev& m = mems[first + blockIdx.y];
-    if (m.np <= 1) return;
-    uint32_t* totals = m.hist + int64_t(256) * sort_tiles(m.np);
-    __shared__ uint32_t s[256];
-    const uint32_t v = totals[threadIdx.x];
-    s[threadIdx.x] = v;
-    __syncthreads();
-    for (int off = 1; off < 256; off <<= 1) {
-        const uint32_t t = int(threadIdx.x) >= off ? s[threadIdx.x - off] : 0u;
-        __syncthreads();
-        s[threadIdx.x] += t;
-        __syncthreads();
-    }
-    totals[threadIdx.x] = s[threadIdx.x] - v;
-}
-
 // Stable scatter of pass `pass`: (key_a, idx_a) -> (key_b, idx_b) for even
-// passes, the reverse for odd ones.
+// passes, the reverse for odd ones.  A wavefront holds 64 kSortRounds keys in a
+// row of their order and counts its digits round after round (the leader of
+// equal digits adds, the wavefront's own atomics keep their order), so a block
+// needs three barriers: totals, counts, offsets.
 __global__ __launch_bounds__(256) void k_radix_scatter(const MemberDev* __restrict__ mems,
-                                                       int first, int pass) {
+                                                       int first, int pass, int bits) {
     const MemberDev& m = mems[first + blockIdx.y];
     const int nb = sort_tiles(m.np);
     if (m.np <= 1 || int(blockIdx.x) >= nb) return;  // uniform per block
@@ -704,36 +742,50 @@ __global__ __launch_bounds__(256) void k_radix_scatter(const MemberDev* __restri
     const uint32_t* vin = odd ? m.idx_b : m.idx_a;
     uint32_t* kout = odd ? m.key_a : m.key_b;
     uint32_t* vout = odd ? m.idx_a : m.idx_b;
-    const int shift = 8 * pass;
-    const uint32_t* hist = m.hist;
-    const uint32_t* totals = m.hist + int64_t(256) * nb;
-    __shared__ uint32_t base[256];
+    const int shift = bits * pass;
+    const uint32_t low = (1u << bits) - 1u;
     __shared__ uint32_t wcnt[4][256];
+    __shared__ uint32_t s[4];
     const int tid = int(threadIdx.x), lane = tid & 63, wave = tid >> 6;
-    base[tid] = totals[tid] + hist[int64_t(tid) * nb + blockIdx.x];
+    const int64_t w0 = int64_t(blockIdx.x) * kSortTile + wave * 64 * kSortRounds + lane;
+    uint32_t k[kSortRounds], v[kSortRounds], rank[kSortRounds];
+#pragma unroll
+    for (int r = 0; r < kSortRounds; ++r) {
+        const int64_t i = w0 + r * 64;
+        k[r] = i < m.np ? kin[i] : 0u;
+        v[r] = i < m.np ? vin[i] : 0u;
+    }
     for (int w = 0; w < 4; ++w) wcnt[w][tid] = 0;
-    __syncthreads();
+    // where this block's keys of digit tid go
+    uint32_t all;
+    const uint32_t base = block_scan(m.hist[int64_t(256) * nb + tid], s, &all) +
+                          m.hist[int64_t(tid) * nb + blockIdx.x];   // (a barrier inside)
     const unsigned long long lt = (1ull << lane) - 1ull;
-    const int64_t b0 = int64_t(blockIdx.x) * kSortTile;
-    for (int r = 0; r < kSortTile / 256; ++r) {
-        const int64_t i = b0 + r * 256 + tid;
-        const bool valid = i < m.np;
-        const uint32_t k = valid ? kin[i] : 0u;
-        const uint32_t d = (k >> shift) & 255u;
-        const unsigned long long mask = match_digit(d, valid);
-        const int rank = __popcll(mask & lt);
-        if (valid && rank == 0) wcnt[wave][d] = uint32_t(__popcll(mask));
-        __syncthreads();
-        if (valid) {
-            uint32_t off = base[d] + uint32_t(rank);
-            for (int w = 0; w < wave; ++w) off += wcnt[w][d];
-            kout[off] = k;
-            vout[off] = vin[i];
-        }
-        __syncthreads();
-        base[tid] += wcnt[0][tid] + wcnt[1][tid] + wcnt[2][tid] + wcnt[3][tid];
-        for (int w = 0; w < 4; ++w) wcnt[w][tid] = 0;
-        __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kSortRounds; ++r) {
+        const bool valid = w0 + r * 64 < m.np;
+        const uint32_t d = (k[r] >> shift) & low;
+        const unsigned long long mask = match_digit(d, valid, bits);
+        uint32_t before = 0;
+        if (valid && (mask & lt) == 0)
+            before = atomicAdd(&wcnt[wave][d], uint32_t(__popcll(mask)));
+        rank[r] = uint32_t(__shfl(int(before), valid ? __ffsll(mask) - 1 : lane)) +
+                  uint32_t(__popcll(mask & lt));
+    }
+    __syncthreads();
+    uint32_t off = base;
+    for (int w = 0; w < 4; ++w) {
+        const uint32_t c = wcnt[w][tid];
+        wcnt[w][tid] = off;
+        off += c;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kSortRounds; ++r) {
+        if (w0 + r * 64 >= m.np) continue;
+        const uint32_t o = wcnt[wave][(k[r] >> shift) & low] + rank[r];
+        kout[o] = k[r];
+        vout[o] = v[r];
     }
 }
 
@@ -768,23 +820,42 @@ __global__ void k_copy_back(const MemberDev* __restrict__ mems, int first) {
 
 int sort_blocks(int64_t np) { return int((np + kSortTile - 1) / kSortTile); }
 
-hipError_t launch_particle_sort(const Launch& L, int64_t max_np, int nx, int ny, int nz) {
-    if (max_np <= 1) return hipSuccess;
+// Sorts (key_a, idx_a) in passes of equal digits of at most 8 bits of the
+// Morton key; returns the number of passes.
+static int sort_pairs(const Launch& L, int64_t max_np, int nx, int ny, int nz) {
     const unsigned y = unsigned(L.count);
-    const dim3 g(unsigned((max_np + 255) / 256), y);
     const dim3 t(unsigned(sort_blocks(max_np)), y);
     int axis_bits = 0;
     while ((1 << axis_bits) < std::max(nx, std::max(ny, nz))) ++axis_bits;
-    const int passes = (3 * axis_bits + 7) / 8;   // 8-bit digits of the Morton key
-    k_make_keys<<<g, 256, 0, L.stream>>>(L.members, L.first);
+    const int passes = (3 * axis_bits + 7) / 8, bits = (3 * axis_bits + passes - 1) / passes;
     for (int pass = 0; pass < passes; ++pass) {
-        k_radix_hist<<<t, 256, 0, L.stream>>>(L.members, L.first, pass);
+        k_radix_hist<<<t, 256, 0, L.stream>>>(L.members, L.first, pass, bits);
         k_scan_digit<<<dim3(256, y), 256, 0, L.stream>>>(L.members, L.first);
-        k_scan_totals<<<dim3(1, y), 256, 0, L.stream>>>(L.members, L.first);
-        k_radix_scatter<<<t, 256, 0, L.stream>>>(L.members, L.first, pass);
+        k_radix_scatter<<<t, 256, 0, L.stream>>>(L.members, L.first, pass, bits);
     }
+    return passes;
+}
+
+hipError_t launch_particle_sort(const Launch& L, int64_t max_np, int nx, int ny, int nz) {
+    if (max_np <= 1) return hipSuccess;
+    const dim3 g(unsigned((max_np + 255) / 256), unsigned(L.count));
+    k_make_keys<<<g, 256, 0, L.stream>>>(L.members, L.first);
+    const int passes = sort_pairs(L, max_np, nx, ny, nz);
     k_gather_sorted<<<g, 256, 0, L.stream>>>(L.members, L.first, passes);
     k_copy_back<<<g, 256, 0, L.stream>>>(L.members, L.first);
+    return hipGetLastError();
+}
+
+hipError_t launch_particle_load(const Launch& L, int64_t np, int nx, int ny, int nz,
+                                const float* pos, const float* vel) {
+    if (np <= 0) return hipSuccess;
+    const unsigned g = unsigned((np + 255) / 256);
+    int passes = -1;
+    if (np > 1) {
+        k_load_keys<<<g, 256, 0, L.stream>>>(L.members, L.first, pos);
+        passes = sort_pairs(L, np, nx, ny, nz);
+    }
+    k_load_sorted<<<g, 256, 0, L.stream>>>(L.members, L.first, passes, pos, vel);
     return hipGetLastError();
 }
 

@@ -202,8 +202,9 @@ hipError_t launch_particles(const Launch& L, int prec, int64_t max_np, int mode,
 hipError_t launch_particle_sort(const Launch& L, int64_t max_np, int nx, int ny, int nz);
 hipError_t launch_particle_unsort(hipStream_t s, const MemberDev& m, float* pos_out,
                                   float* vel_out);
-hipError_t launch_particle_upload(hipStream_t s, const MemberDev& m, const float* pos,
-                                  const float* vel);
+// Particles of the caller (AoS) into one member's arrays in sorted order.
+hipError_t launch_particle_load(const Launch& L, int64_t np, int nx, int ny, int nz,
+                                const float* pos, const float* vel);
 
 // ---- vacuum boundary and external potential (isolated.hip) ----
 // Green's function on the padded grid (into pad), then its transform's real
