@@ -118,9 +118,9 @@ __global__ __launch_bounds__((wg_size<typename PlanFor<NX, V>::type, T>())) void
 
 // Vacuum-boundary convolution, x pass on the zero-padded grid (a padded
 // member descriptor: lengths 2n, psi = the padded grid): x forward transform,
-// multiplication by the stored real transform of the padded Green's function
-// (same [x][y][z] layout), x inverse transform, in one pass as P7 does.  Only
-// the x < NX/2 half is read (the padding half holds zeros and is never
+// multiplication by the stored real transform of the padded Green's function,
+// x inverse transform, in one pass as P7 does.  The z modes 0..nz, vac_pitch
+// elements a row (see k_vac_fft).  Only the x < NX/2 half is read (the padding half holds zeros and is never
 // written) and only that half of the result, the one the potential needs, is
 // stored.
 template <int NX, typename T, int V>
@@ -136,18 +136,18 @@ __global__ __launch_bounds__((wg_size<typename PlanFor<NX, V>::type, T>())) void
     __syncthreads();
     const LN ln;
     // element offsets fit 32 bits: at most 512 * 512 * 512 per padded grid
-    const int plane = m.ny * m.nz;
+    const int pitch = vac_pitch(m.nz), plane = m.ny * pitch;
     const int q = int(blockIdx.x) * LN::PP + ln.p;
-    const bool ok = q < plane;
+    const int qy = q / pitch, qz = q - qy * pitch;
+    const bool ok = q < plane && qz <= m.nz / 2;
     cplx<T>* lane = static_cast<cplx<T>*>(m.psi) + q;
     constexpr int HALF = NX / 2;
     // The Green's factors are even in each wavenumber and stored for modes
     // 0..n of each axis (n = half the padded length): mode k > n reads 2n - k.
     const int hy = m.ny / 2, hz = m.nz / 2;
-    const int qy = q / m.nz, qz = q - qy * m.nz;
     const int gplane = (hy + 1) * (hz + 1);
     const T* green = static_cast<const T*>(m.green) +
-                     (min(qy, m.ny - qy) * (hz + 1) + min(qz, m.nz - qz));
+                     (min(qy, m.ny - qy) * (hz + 1) + qz);
     // the Green's factors of this lane's output slots are loaded with the data
     T gv[FP::E];
     cplx<T> v[FP::E];
@@ -275,7 +275,7 @@ struct XMulGreen {
     template <typename T>
     static hipError_t go(const Launch& L, int ny, int nz) {
         constexpr int V = 0;   // the second plan measured slower on the padded 512 axis
-        dim3 grid(unsigned(tiles<NX, T, V>(int64_t(ny) * nz)), unsigned(L.count));
+        dim3 grid(unsigned(tiles<NX, T, V>(int64_t(ny) * vac_pitch(nz))), unsigned(L.count));
         k_x_mul_green<NX, T, V><<<grid, block<NX, T, V>(), 0, L.stream>>>(L.members, L.first);
         return hipGetLastError();
     }

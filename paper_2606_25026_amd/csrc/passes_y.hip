@@ -196,7 +196,9 @@ struct RestrictFft {
 // quarter of the padded grid that can be non-zero before the x pass (x < nx,
 // y < ny) is read or written along z, and the y passes see the y >= ny half of
 // each pencil as zeros (forward) or do not store it (inverse), so the padded
-// grid's y >= ny rows are never touched:
+// grid's y >= ny rows are never touched.  The rows hold the modes 0..nz of a real
+// row's spectrum, vac_pitch elements apart (all 2 nz of them, 19 + 18 + 11 + 11 us
+// for the four and 41 for the x pass at 128^3; now 14 + 15 + 10 + 10 and 28):
 //   kVacZFwd  the density rows (real, nz values, held in Phi) zero-extended to
 //             2 nz, forward z transform into the padded rows (x < nx, y < ny);
 //   kVacYFwd  forward y transform of the x < nx pencils, inputs y >= ny zero;
@@ -223,10 +225,10 @@ __global__ __launch_bounds__((wg_size<typename PlanFor<N>::type, T>())) void k_v
     cplx<T>* pad = static_cast<cplx<T>*>(m.psi);
     cplx<T> v[FP::E];
     if constexpr (STRIDED) {
-        // y pencils of the padded [2nx][2ny][2nz] grid with x < nx: q = x 2nz + z
-        const int64_t pny = m.ny, pnz = m.nz;
+        // y pencils of the padded [nx][2ny][pitch] rows: q = x pitch + z, z <= nz
+        const int64_t pny = m.ny, pnz = vac_pitch(m.nz);
         const int64_t count = int64_t(m.nx / 2) * pnz;
-        const bool ok = q < count;
+        const bool ok = q < count && q % pnz <= m.nz / 2;
         const int64_t b = ok ? (q / pnz) * (pny * pnz) + (q % pnz) : 0;
         cplx<T>* lane = pad + (b + int64_t(ln.t) * pnz);
 #pragma unroll
@@ -249,7 +251,7 @@ __global__ __launch_bounds__((wg_size<typename PlanFor<N>::type, T>())) void k_v
         const int rnx = m.nx / 2, rny = m.ny / 2;
         const bool ok = q < int64_t(rnx) * rny;
         const int64_t x = ok ? q / rny : 0, y = ok ? q - x * rny : 0;
-        const int64_t pb = (x * m.ny + y) * m.nz;      // padded row
+        cplx<T>* row = pad + (x * m.ny + y) * vac_pitch(N);   // padded row
         T* phi = static_cast<T*>(m.phi) + (ok ? q : 0) * H;
         if constexpr (MODE == kVacZFwd) {
 #pragma unroll
@@ -258,9 +260,20 @@ __global__ __launch_bounds__((wg_size<typename PlanFor<N>::type, T>())) void k_v
                 v[s] = cplx<T>{(ok && e < H) ? gldr(phi, e) : T(0), T(0)};
             }
             pencil_fft<FP, false, T>(v, lds, tw, ln.t, ln);
-            store_slots<FP, FP::last()>(v, pad, pb, 1, ok, ln);
+            if (!ok) return;
+#pragma unroll
+            for (int s = 0; s < FP::E; ++s) {
+                const int e = slot_elem<FP, FP::last()>(ln.t, s);
+                if (e <= H) gst(row, e, v[s]);
+            }
         } else {
-            load_slots<FP, FP::first()>(v, pad, pb, 1, ok, ln);
+            // the modes above nz are the conjugates of those below
+#pragma unroll
+            for (int s = 0; s < FP::E; ++s) {
+                const int e = slot_elem<FP, FP::first()>(ln.t, s);
+                v[s] = ok ? gld(row, e <= H ? e : N - e) : cplx<T>{T(0), T(0)};
+                if (e > H) v[s].im = -v[s].im;
+            }
             pencil_fft<FP, true, T>(v, lds, tw, ln.t, ln);
             if (!ok) return;
 #pragma unroll
@@ -388,7 +401,7 @@ hipError_t launch_vac_fft(const Launch& L, int prec, int nx, int ny, int nz, int
     // nx, ny, nz: the padded lengths
     if (mode == kVacZFwd || mode == kVacZInv)
         return dispatch_n<VacFft>(nz, L, prec, int64_t(nx / 2) * (ny / 2), mode);
-    return dispatch_n<VacFft>(ny, L, prec, int64_t(nx / 2) * nz, mode);
+    return dispatch_n<VacFft>(ny, L, prec, int64_t(nx / 2) * vac_pitch(nz), mode);
 }
 
 int64_t axis_tiles(int n, int64_t pencils, int prec) {
