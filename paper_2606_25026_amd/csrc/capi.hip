@@ -723,7 +723,7 @@ wdm_status wdm_plan_create(const wdm_config* members, int32_t n_members, void* w
         if (launch_zero(p->stream, m.rho_b, size_t(cells) * (p->prec ? 8 : 4)) != hipSuccess ||
             launch_zero(p->stream, m.dt, 4 * sizeof(double)) != hipSuccess ||
             launch_zero(p->stream, m.results, kRedFields * sizeof(double)) != hipSuccess ||
-            launch_zero(p->stream, m.watch, (2 * m.watch_n + 2) * sizeof(unsigned long long)) !=
+            launch_zero(p->stream, m.watch, (2 * m.watch_n + 3) * sizeof(unsigned long long)) !=
                 hipSuccess ||
             launch_zero(p->stream, m.stab, 2 * sizeof(double)) != hipSuccess ||
             (m.rho_fx && launch_zero(p->stream, m.rho_fx, size_t(cells) * 8) != hipSuccess))
@@ -731,7 +731,8 @@ wdm_status wdm_plan_create(const wdm_config* members, int32_t n_members, void* w
     }
     // absorbing factors of dt = 0 (all ones) until the first step sets dt
     for (const auto& c : p->classes)
-        if (launch_absorb_tables(Launch{p->stream, p->table, c.first, c.count}) != hipSuccess ||
+        if (launch_open_run(Launch{p->stream, p->table, c.first, c.count}, p->prec,
+                            int64_t(c.nx) + int64_t(c.ny) * c.nz, 0.0, false, true) != hipSuccess ||
             launch_kx2_tables(Launch{p->stream, p->table, c.first, c.count}) != hipSuccess)
             return cleanup(WDM_EDEVICE, "plan initialisation failed");
     // no external potential until one is set
@@ -780,7 +781,7 @@ wdm_status wdm_set_state(wdm_plan* p, int32_t member, const void* psi, const flo
     HIPCHK(hipMemcpyAsync(m.psi, psi, size_t(n) * (p->prec ? 16 : 8), hipMemcpyDeviceToDevice,
                           p->stream));
     HIPCHK(launch_zero(p->stream, m.rho_b, size_t(n) * (p->prec ? 8 : 4)));
-    HIPCHK(launch_zero(p->stream, m.watch, (2 * m.watch_n + 2) * sizeof(unsigned long long)));
+    HIPCHK(launch_zero(p->stream, m.watch, (2 * m.watch_n + 3) * sizeof(unsigned long long)));
     HIPCHK(launch_zero(p->stream, m.stab, 2 * sizeof(double)));
     if (c.n_particles > 0) {
         HIPCHK(launch_particle_load(L, c.n_particles, c.nx, c.ny, c.nz, pos, vel));
@@ -944,8 +945,7 @@ hipError_t enqueue_close(wdm_plan* p, hipStream_t s, int64_t n) {
             e = timed(p, kKCloseParticles, [&] {
                 return launch_particles(L, p->prec, c.moving_np, 1, kHalfKick, p->det);
             });
-        if (e == hipSuccess) e = launch_advance_time(L, n);
-        if (e == hipSuccess) e = launch_stability(L, watch_slots(c.nx, c.ny), kCKin);
+        if (e == hipSuccess) e = launch_close_run(L, watch_slots(c.nx, c.ny), kCKin, n);
         if (e != hipSuccess) return e;
     }
     return e;
@@ -1030,11 +1030,27 @@ void drop_graphs(wdm_plan* p) {
 // What follows a run of steps.
 enum After : int { kNoApply = 0, kApplyAfter = 1, kBlockGraph = 2 };
 
+// Whether n steps run faster replayed than launched one by one.  A replay costs
+// about 30 us more at the start of a call (the hop to the plan's own stream and
+// back, the first graph's launch) and saves some 7 us a step where particles
+// fork onto the second stream; without them a step is four launches in a row,
+// which one stream takes faster than a graph's nodes.  Measured, replayed against
+// direct, in us a call: 32^3 without particles 70 / 46 for one step and 839 / 710
+// for 32, 256^3 370 / 339 and 8012 / 7792; 64^3 + 2e4 96 / 86 for one, 141 / 129
+// for two, 183 / 184 for three, 1467 / 1599 for 32; 128^3 + 1e6 156 / 143, 238 /
+// 236, 321 / 328, 2760 / 3079.
+bool replay_pays(const wdm_plan* p, int64_t n) {
+    for (const auto& c : p->classes)
+        if (c.moving_np > 0) return n > 2;
+    return false;
+}
+
 // n steps: opening half kick, n - 1 merged steps, closing half kick, then the
 // corrector when `after` asks for it (kBlockGraph: the n = every steps and the
 // corrector replayed as the one block graph).
 wdm_status run_steps(wdm_plan* p, int64_t n, double dt, After after) {
-    const bool graphs = p->use_graphs && !p->profiling;
+    const bool graphs =
+        p->use_graphs && !p->profiling && (after == kBlockGraph || replay_pays(p, n));
     if (graphs) {
         bool ok = true;
         for (int w = 0; w < 3 && ok; ++w) ok = capture_step(p, w) == hipSuccess;
@@ -1063,9 +1079,8 @@ wdm_status run_steps(wdm_plan* p, int64_t n, double dt, After after) {
     }
     for (const auto& c : p->classes) {
         const Launch L{s, p->table, c.first, c.count};
-        HIPCHK(dt != 0.0 ? launch_set_dt(L, dt, 0) : launch_set_dt(L, 0.0, 1));
-        HIPCHK(launch_kinetic_tables(L, p->prec, int64_t(c.nx) + int64_t(c.ny) * c.nz));
-        if (c.absorb) HIPCHK(launch_absorb_tables(L));
+        HIPCHK(launch_open_run(L, p->prec, int64_t(c.nx) + int64_t(c.ny) * c.nz, dt, dt == 0.0,
+                               c.absorb));
     }
     if (after == kBlockGraph) {
         // a re-sort due inside the block is done before it

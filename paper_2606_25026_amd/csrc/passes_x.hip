@@ -288,24 +288,50 @@ hipError_t launch_x_mul_green(const Launch& L, int prec, int nx, int ny, int nz)
     return dispatch_n<XMulGreen>(nx, L, prec, ny, nz);
 }
 
-// The kinetic factor tables of the dt in use, for every member of the class
-// (grid-stride over nx + ny nz entries per member).
-template <typename T>
-__global__ __launch_bounds__(256) void k_kinetic_tables(const MemberDev* __restrict__ mems,
-                                                        int first) {
-    const MemberDev& m = mems[first + blockIdx.y];
-    write_kinetic_table<T>(m, gldr(m.dt, 0), int64_t(gridDim.x) * blockDim.x,
-                           int64_t(blockIdx.x) * blockDim.x + threadIdx.x);
+// b_a[i] = exp(-alpha dt g_a(i L_a / n_a)) with the face profile of Sec. 3.1,
+// g(x) = 2 - tanh(x / w) + tanh((x - L) / w), w = L / n_b, on nodes x in
+// [0, L) (the paper centres the box: its x + L/2 is our x); entry i of the x, y
+// and z nodes in turn.  All ones where alpha dt is 0.
+__device__ __forceinline__ double absorb_entry(const MemberDev& m, double dt, int i) {
+    const double adt = m.absorb_alpha * dt;
+    if (adt == 0.0) return 1.0;
+    const int nxy = m.nx + m.ny;
+    const int k = i < m.nx ? i : (i < nxy ? i - m.nx : i - nxy);
+    const int len = i < m.nx ? m.nx : (i < nxy ? m.ny : m.nz);
+    const double L = i < m.nx ? m.lx : (i < nxy ? m.ly : m.lz);
+    const double w = L / m.absorb_nb;
+    const double x = double(k) * (L / double(len));
+    return exp(-adt * (2.0 - tanh(x / w) + tanh((x - L) / w)));
 }
 
-hipError_t launch_kinetic_tables(const Launch& L, int prec, int64_t max_entries) {
+// What a run of steps needs first, for every member of the class in one launch:
+// the dt in use (own: the member's own or automatic one) and the tables made
+// from it, the kinetic factors (grid-stride over nx + ny nz entries) and the
+// absorbing boundary's.
+template <typename T>
+__global__ __launch_bounds__(256) void k_open_run(const MemberDev* __restrict__ mems, int first,
+                                                  double given, int own, int absorb) {
+    const MemberDev& m = mems[first + blockIdx.y];
+    const double user = gldr(m.dt, 2);
+    const double dt = !own ? given : user != 0.0 ? user : gldr(m.dt, 1);
+    const int64_t threads = int64_t(gridDim.x) * blockDim.x;
+    const int64_t id = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (id == 0) gstr(m.dt, 0, dt);
+    if (absorb)
+        for (int64_t i = id; i < m.nx + m.ny + m.nz; i += threads)
+            gstr(m.absorb, i, absorb_entry(m, dt, int(i)));
+    write_kinetic_table<T>(m, dt, threads, id);
+}
+
+hipError_t launch_open_run(const Launch& L, int prec, int64_t max_entries, double dt, bool own,
+                           bool absorb) {
     int64_t g = (max_entries + 255) / 256;
     if (g > 1024) g = 1024;
     const dim3 grid(unsigned(g), unsigned(L.count));
     if (prec)
-        k_kinetic_tables<double><<<grid, 256, 0, L.stream>>>(L.members, L.first);
+        k_open_run<double><<<grid, 256, 0, L.stream>>>(L.members, L.first, dt, own, absorb);
     else
-        k_kinetic_tables<float><<<grid, 256, 0, L.stream>>>(L.members, L.first);
+        k_open_run<float><<<grid, 256, 0, L.stream>>>(L.members, L.first, dt, own, absorb);
     return hipGetLastError();
 }
 

@@ -89,8 +89,8 @@ struct MemberDev {
     // |Phi|, [watch_n, 2 watch_n) the largest |psi|^2 (kicks with a
     // self-interaction only), as FP64 bit patterns compared as unsigned
     // integers (NaN above +inf), one slot per wavefront of the launch (no two
-    // wavefronts share a slot); [2 watch_n, 2 watch_n + 2) the two maxima
-    // folded by the check; all cleared by each check
+    // wavefronts share a slot); [2 watch_n, 2 watch_n + 3) the two maxima
+    // folded by the check and its ticket; all cleared by each check
     unsigned long long* watch;
     int64_t watch_n;
     // [0] largest |dt| / dt_max (Sec. 3.5) over the steps checked since
@@ -141,9 +141,12 @@ hipError_t launch_y_fft_psi(const Launch& L, int prec, int nx, int ny, int nz, b
                             int variant = 0);
 hipError_t launch_y_fft_spec(const Launch& L, int prec, int nx, int ny, int nz, bool inverse,
                              int variant = 0);
-// Kinetic factor tables e_x, e_yz / N of the dt in use (dt[0]) for every member
-// of the class; max_entries = the largest nx + ny nz of the class.
-hipError_t launch_kinetic_tables(const Launch& L, int prec, int64_t max_entries);
+// Start of a run of steps, for every member of the class: the dt in use (dt[0] =
+// dt, or with `own` the member's user or automatic one), the kinetic factor tables
+// e_x, e_yz / N and, with `absorb`, the absorbing boundary's; max_entries = the
+// largest nx + ny nz of the class.
+hipError_t launch_open_run(const Launch& L, int prec, int64_t max_entries, double dt, bool own,
+                           bool absorb);
 // k_x^2 of every member of the class (xtab).
 hipError_t launch_kx2_tables(const Launch& L);
 // P3: x forward, kinetic phase exp(-i eta |k|^2 dt/2)/N, x inverse.
@@ -238,20 +241,17 @@ hipError_t launch_reduce_finish(const Launch& L, unsigned fields, int nblocks);
 hipError_t launch_reduce_particles(const Launch& L, int64_t max_np);
 hipError_t launch_dt_auto(const Launch& L, double zeta, double c_kin);
 hipError_t launch_set_dt(const Launch& L, double dt, int mode);
-// Absorbing-boundary factor tables of every member of the class from dt[0]
-// (all ones where absorb_alpha is 0).
-hipError_t launch_absorb_tables(const Launch& L);
-hipError_t launch_advance_time(const Launch& L, int64_t nsteps);
 // Slots of the stability watch per member: at least the wavefronts of any P1
 // launch (one pencil or more per wavefront).
 inline int64_t watch_slots(int nx, int ny) { return int64_t(nx) * ny + 1024; }
 // 64-bit words of a member's watch: the two slot halves and their two totals.
-inline int64_t watch_words(int nx, int ny) { return 2 * watch_slots(nx, ny) + 2; }
-// Stability check after a wdm_step call: folds the watch slots (`slots` =
+inline int64_t watch_words(int nx, int ny) { return 2 * watch_slots(nx, ny) + 3; }
+// The end of a wdm_step call: the time advanced by nsteps, and the stability
+// check, which folds the watch slots (`slots` =
 // watch_n of the class) into stab (|dt| / dt_max with dt_max = 0.5 min{c_kin
 // dx^2 / eta, 2 pi eta / max|Phi|, 2 pi eta / (|kappa| max|psi|^2)}, Sec. 3.5)
 // and clears them.
-hipError_t launch_stability(const Launch& L, int64_t slots, double c_kin);
+hipError_t launch_close_run(const Launch& L, int64_t slots, double c_kin, int64_t nsteps);
 hipError_t launch_zero(hipStream_t s, void* p, size_t bytes);
 hipError_t launch_copy_complex(hipStream_t s, void* dst, const void* src, int64_t n,
                                int dst_prec, int src_prec);
