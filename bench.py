@@ -33,7 +33,7 @@ HBM_PEAK_GBS = 8000.0
 # algorithmic HBM bytes per cell (grid passes) and per particle
 BYTES_PER_CELL = {
     "z_potential_kick": 24, "y_fft_psi_fwd": 16, "x_kinetic": 16, "y_fft_psi_inv": 16,
-    "z_density_r2c": 28, "y_fft_spec_fwd": 8, "x_green": 8, "y_fft_spec_inv": 8,
+    "z_density_r2c": 24, "y_fft_spec_fwd": 8, "x_green": 8, "y_fft_spec_inv": 8,
     "z_potential_close_kick": 24,
     # the plane passes of the four-pass step
     "xy_kinetic": 16, "xy_green": 8,
@@ -56,8 +56,8 @@ def pass_variant(name, tuning):
 OVERLAPS_PARTICLES = {"y_fft_psi_fwd", "x_kinetic", "y_fft_psi_inv", "xy_kinetic"}
 # algorithmic bytes per cell of a step: the four-pass form (all-default plan
 # tables on the grids that have it), or the eight-pass one
-STEP_BYTES_PER_CELL = 76
-STEP_BYTES_PER_CELL_EIGHT = 124
+STEP_BYTES_PER_CELL = 72
+STEP_BYTES_PER_CELL_EIGHT = 120
 STEP_BYTES_PER_PARTICLE = 48
 
 

@@ -95,9 +95,10 @@ __global__ __launch_bounds__((wg_size<typename PlanFor<NZ, V>::type, T>())) void
             for (int s = 0; s < FP::E; ++s) phi[s] += gldr(ge, slot_elem<FP, FP::first()>(ln.t, s));
         }
     }
+    if (ok && (OP != kZKickFft || phi_wanted(m))) {
 #pragma unroll
-    for (int s = 0; s < FP::E; ++s)
-        if (ok) gstr(gphi, slot_elem<FP, FP::first()>(ln.t, s), phi[s]);
+        for (int s = 0; s < FP::E; ++s) gstr(gphi, slot_elem<FP, FP::first()>(ln.t, s), phi[s]);
+    }
     // lanes past the last pencil hold zeros here
     watch_max<FP::E>(m.watch, m.watch_n, phi);
     if constexpr (OP == kZPhiOnly) return;
@@ -199,7 +200,7 @@ __global__ __launch_bounds__((wg_size<typename PlanFor<NZ, V>::type, T>())) void
 #pragma unroll
         for (int s = 0; s < FP::E; ++s) {
             v[s] = cplx<T>{v[s].re * v[s].re + v[s].im * v[s].im + rbv[s], T(0)};
-            if (clear) gstr(rb, slot_const<FP, FP::first()>(s), T(0));
+            if (clear && rbv[s] != T(0)) gstr(rb, slot_const<FP, FP::first()>(s), T(0));
         }
         if constexpr (TO_PHI) {
             if (ok) {

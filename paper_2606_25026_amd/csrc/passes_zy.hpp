@@ -6,11 +6,10 @@
 // one row; loads, stores and the z transform) and "columns" (a lane has the R1
 // rows' values at one z; the y radix, and loads and stores of the (y0, k1)
 // form, whose lanes run along z).  An LDS exchange turns one into the other.
-// P1 moves 24 and P5 28 bytes per cell; at 256^3 P1 takes 80 us (its vector
-// units two thirds busy, its LDS a third) and P5 60 without particles.  Every
-// transform
-// and exchange below ends with a barrier after its last LDS read, so the next
-// one may write at once.
+// P1 moves 24 bytes per cell (20 where no particle needs Phi) and P5 24; at 256^3
+// P1 takes 80 us (its vector units two thirds busy, its LDS a third) and P5 60
+// without particles.  Every transform and exchange below ends with a barrier after
+// its last LDS read, so the next one may write at once.
 #pragma once
 #include "passes_split.hpp"
 
@@ -203,8 +202,10 @@ __global__ __launch_bounds__((ZRows<NZ, R1>::WG)) void k_zy_potential_kick(
             for (int s = 0; s < FP::E; ++s) phi[s] += gldr(ge, slot_elem<FP, FP::first()>(zc.t, s));
         }
     }
+    if (OP != kZKickFft || phi_wanted(m)) {
 #pragma unroll
-    for (int s = 0; s < FP::E; ++s) gstr(gphi, slot_elem<FP, FP::first()>(zc.t, s), phi[s]);
+        for (int s = 0; s < FP::E; ++s) gstr(gphi, slot_elem<FP, FP::first()>(zc.t, s), phi[s]);
+    }
     watch_max<FP::E>(m.watch, m.watch_n, phi);
     if constexpr (OP == kZPhiOnly) return;
     const double dt = gldr(m.dt, 0);
@@ -366,7 +367,8 @@ __global__ __launch_bounds__((ZRows<NZ, R1>::WG)) void k_zy_density(
 #pragma unroll
     for (int s = 0; s < FP::E; ++s) {
         v[s] = cplx<T>{v[s].re * v[s].re + v[s].im * v[s].im + rbv[s], T(0)};
-        if (clear) gstr(rb, slot_const<FP, FP::first()>(s), T(0));
+        // (most of a grid holds no baryons: 4 bytes a cell not written)
+        if (clear && rbv[s] != T(0)) gstr(rb, slot_const<FP, FP::first()>(s), T(0));
     }
     pencil_fft<FP, false, T>(v, lds, tw, zc.t, zc);
     // pencils -> columns of the half spectrum.  The density is real, so the
