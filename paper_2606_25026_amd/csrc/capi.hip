@@ -24,9 +24,9 @@ hipError_t conv_backward_weight(hipStream_t s, int layer, const uint16_t* dz,
                                 float* gb, int n);
 int wgrad_part_floats();
 hipError_t net_pack_input(hipStream_t s, const float* x, uint16_t* y, int64_t cells, int cin,
-                          int cp, const double* scales);
+                          const double* scales);
 hipError_t net_mse(hipStream_t s, const float* y, const float* t, uint16_t* dy, double* part,
-                   double* out, int64_t cells, int cout, int cp, const double* s_out);
+                   double* out, int64_t cells, const double* s_out);
 hipError_t net_adam(hipStream_t s, float* w, const float* g, float* m, float* v, int n, float lr,
                     float b1, float b2, float eps, float c1, float c2);
 hipError_t net_pack_weights(hipStream_t s, const float* w, uint16_t* fwd, uint16_t* bwd, int cin,
@@ -1750,7 +1750,7 @@ hipError_t net_run_layers(wdm_net* net, hipStream_t s) {
 hipError_t net_run_forward(wdm_net* net, const float* x, float* y) {
     hipStream_t s = net->stream;
     hipError_t e;
-    if ((e = net_pack_input(s, x, net->at<uint16_t>(net->L.x0), net->cells, 3, 4,
+    if ((e = net_pack_input(s, x, net->at<uint16_t>(net->L.x0), net->cells, 3,
                             net->at<double>(net->L.scal) + 3)) != hipSuccess)
         return e;
     if ((e = net_run_layers(net, s)) != hipSuccess) return e;
@@ -1872,7 +1872,7 @@ wdm_status wdm_net_forward(wdm_net* net, const float* x, float* y) {
 wdm_status wdm_net_backward(wdm_net* net, const float* dy) {
     if (!net || !dy) return fail(WDM_EINVAL, "null argument");
     if (!net->have_forward) return fail(WDM_ESTATE, "backward needs a forward pass first");
-    HIPCHK(net_pack_input(net->stream, dy, net->at<uint16_t>(net->L.dy), net->cells, 2, 4,
+    HIPCHK(net_pack_input(net->stream, dy, net->at<uint16_t>(net->L.dy), net->cells, 2,
                           nullptr));
     HIPCHK(net_run_backward(net));
     return WDM_OK;
@@ -1883,7 +1883,7 @@ wdm_status wdm_net_mse_backward(wdm_net* net, const float* target, double* loss)
     if (!net->have_forward) return fail(WDM_ESTATE, "backward needs a forward pass first");
     double* scal = net->at<double>(net->L.scal);
     HIPCHK(net_mse(net->stream, net->at<float>(net->L.y), target, net->at<uint16_t>(net->L.dy),
-                   net->at<double>(net->L.dpart), scal, net->cells, 2, 4, scal + 5));
+                   net->at<double>(net->L.dpart), scal, net->cells, scal + 5));
     HIPCHK(net_run_backward(net));
     if (loss) {
         HIPCHK(hipMemcpyAsync(loss, scal, sizeof(double), hipMemcpyDeviceToHost, net->stream));

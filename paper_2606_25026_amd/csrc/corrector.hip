@@ -73,9 +73,6 @@ constexpr int kCTX = 4, kCTY = 4, kCTZ = 16;
 constexpr int kCBX = kCTX + 2, kCBY = kCTY + 2, kCBZ = kCTZ + 2;
 constexpr int kCBrick = kCBX * kCBY * kCBZ;
 
-// v in [-1, n + kCTZ]: periodic index in [0, n)
-__device__ __forceinline__ int wrap_edge(int v, int n) { return (v + n) % n; }
-
 // The input brick of tile t: every 8-byte word of its cells (one 16-byte half
 // cell per thread and slot for 16 channels, one 8-byte cell for 4), loaded into
 // registers; stored to LDS by brick_store.
@@ -89,26 +86,60 @@ struct BrickRegs {
     uint64_t w[W8 == 4 ? 1 : kIt];
 };
 
+// Tile t's first cell.
+struct ConvTile {
+    int x0, y0, z0;
+    __device__ __forceinline__ ConvTile(int t, int ty, int tz) {
+        const int r = t / tz, q = r / ty;
+        x0 = q * kCTX;
+        y0 = (r - q * ty) * kCTY;
+        z0 = (t - r * tz) * kCTZ;
+    }
+};
+
+// The brick cell of each of this lane's loads, one byte a coordinate: the same in
+// every tile, so a load's address is six additions and compares (with the cell
+// and its three wraps found by division each time the address work of a tile was
+// more than its MFMAs': 16 -> 16 channels at 128^3 64 and 71 us, now 57 and 64).
+template <int W8>
+struct BrickCells {
+    using B = BrickRegs<W8>;
+    int cell[B::kIt];
+    __device__ __forceinline__ BrickCells() {
+#pragma unroll
+        for (int k = 0; k < B::kIt; ++k) {
+            const int c = (int(threadIdx.x) + k * 256) / (W8 / B::kPer);
+            const int rr = c / kCBZ, bx = rr / kCBY;
+            cell[k] = bx << 16 | (rr - bx * kCBY) << 8 | (c - rr * kCBZ);
+        }
+    }
+};
+
+// v in [-1, n + kCTZ]: the periodic index, inside the grid; beyond the first node
+// past the end any (no valid output reads it).
+__device__ __forceinline__ int wrap_edge(int v, int n) {
+    return v < 0 ? v + n : min(v >= n ? v - n : v, n - 1);
+}
+
 template <int CPIN, int W8>
-__device__ __forceinline__ void brick_load(BrickRegs<W8>& R, const uint16_t* __restrict__ in,
-                                           int64_t t, int n, int tz, int ty) {
+__device__ __forceinline__ void brick_load(BrickRegs<W8>& R, const BrickCells<W8>& C,
+                                           const uint16_t* __restrict__ in, const ConvTile& t,
+                                           int n) {
     using B = BrickRegs<W8>;
     const int tid = int(threadIdx.x);
-    const int iz = int(t % tz);
-    const int64_t r = t / tz;
-    const int x0 = int(r / ty) * kCTX, y0 = int(r % ty) * kCTY, z0 = iz * kCTZ;
 #pragma unroll
     for (int k = 0; k < B::kIt; ++k) {
         const int i = tid + k * 256;
         if (i < B::kLoads) {
-            const int c = i / (W8 / B::kPer), bz = c % kCBZ, rr = c / kCBZ, by = rr % kCBY,
-                      bx = rr / kCBY;
-            const int64_t g = (int64_t(wrap_edge(x0 + bx - 1, n)) * n +
-                               wrap_edge(y0 + by - 1, n)) * n + wrap_edge(z0 + bz - 1, n);
+            const int c = C.cell[k];
+            // (a cell's channels end below 2^32 bytes: n <= 512)
+            const uint32_t g = uint32_t((wrap_edge(t.x0 + (c >> 16) - 1, n) * n +
+                                         wrap_edge(t.y0 + (c >> 8 & 255) - 1, n)) * n +
+                                        wrap_edge(t.z0 + (c & 255) - 1, n));
             if constexpr (W8 == 4)
-                R.v[k] = *(const WDM_GAS u32x4*)(in + g * CPIN + (i & 1) * 8);
+                R.v[k] = *(const WDM_GAS u32x4*)(in + uint64_t(g) * CPIN + (i & 1) * 8);
             else
-                R.w[k] = *(const WDM_GAS uint64_t*)(in + g * CPIN);
+                R.w[k] = *(const WDM_GAS uint64_t*)(in + uint64_t(g) * CPIN);
         }
     }
 }
@@ -135,6 +166,10 @@ __device__ __forceinline__ void brick_store(const BrickRegs<W8>& R, uint64_t* br
 // tile's brick is loaded into registers while the current one is computed.
 // The layer's weights (the MFMA A operand) sit in LDS, rows padded by four
 // entries so the sixteen rows a wavefront reads fall on different banks.
+// Two output channels (FEW) would leave 14 of the MFMA's 16 rows empty: its rows
+// are then the channels of the three dy taps, a brick row is multiplied once for
+// all of them, and the three partial sums of an output meet by two lane swaps:
+// 54 products of a wavefront's tile instead of 108, 54 -> 43 us at 128^3.
 template <int CPIN, int COUT, int CPOUT, int EPI>
 __global__ __launch_bounds__(256, 3) void k_conv(const uint16_t* __restrict__ in,
                                                  const uint16_t* __restrict__ wmat,
@@ -164,23 +199,49 @@ __global__ __launch_bounds__(256, 3) void k_conv(const uint16_t* __restrict__ in
         return a;
     };
     const int tx = (n + kCTX - 1) / kCTX, ty = (n + kCTY - 1) / kCTY, tz = (n + kCTZ - 1) / kCTZ;
-    const int64_t ntiles = int64_t(tx) * ty * tz;
+    const int ntiles = tx * ty * tz;
+    const BrickCells<W8> cells;
     BrickRegs<W8> R;
-    if (int64_t(blockIdx.x) < ntiles) brick_load<CPIN, W8>(R, in, blockIdx.x, n, tz, ty);
+    if (int(blockIdx.x) < ntiles)
+        brick_load<CPIN, W8>(R, cells, in, ConvTile(int(blockIdx.x), ty, tz), n);
     double mass = 0.0;   // kEpiApply: this lane's cells, in tile order
     const float s_out = EPI == kEpiApply ? float(gldr(scal, 5)) : 0.0f;
-    for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
-        const int iz = int(t % tz);
-        const int64_t r = t / tz;
-        const int x0 = int(r / ty) * kCTX, y0 = int(r % ty) * kCTY, z0 = iz * kCTZ;
+    for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
+        const ConvTile tile(t, ty, tz);
+        const int x0 = tile.x0, y0 = tile.y0, z0 = tile.z0;
         brick_store<W8>(R, brick);
         __syncthreads();
-        if (t + gridDim.x < ntiles) brick_load<CPIN, W8>(R, in, t + gridDim.x, n, tz, ty);
+        const int next = t + int(gridDim.x);
+        if (next < ntiles) brick_load<CPIN, W8>(R, cells, in, ConvTile(next, ty, tz), n);
         // wavefront `wave` owns x = x0 + wave, y = y0 + s (s < 4), z = z0 + col
-        f32x4 acc[kCTY];
+        constexpr bool FEW = COUT == 2 && CPIN == 16;
+        constexpr int NACC = FEW ? kCTY + 2 : kCTY;
+        f32x4 acc[NACC];
 #pragma unroll
-        for (int s2 = 0; s2 < kCTY; ++s2) acc[s2] = f32x4{0.f, 0.f, 0.f, 0.f};
-        if constexpr (CPIN == 16) {
+        for (int s2 = 0; s2 < NACC; ++s2) acc[s2] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if constexpr (FEW) {
+            // row 4 dy + o of A: channel o (rows 2 and 3 of the weights are zero)
+            // of tap (dx, dy, dz); acc[rr]: brick row rr, lane group dy
+            const int dy = min(col >> 2, 2);
+#pragma unroll
+            for (int dx = 0; dx < 3; ++dx)
+#pragma unroll
+                for (int dz = 0; dz < 3; ++dz) {
+                    uint64_t w = *reinterpret_cast<const uint64_t*>(
+                        &wl[(col & 3) * KW + (dx * 9 + dy * 3 + dz) * 16 + 4 * kq]);
+                    if (col >= 12) w = 0;
+                    bf16x4 a;
+                    __builtin_memcpy(&a, &w, sizeof(a));
+#pragma unroll
+                    for (int rr = 0; rr < kCTY + 2; ++rr) {
+                        const uint64_t bw =
+                            brick[(((wave + dx) * kCBY + rr) * kCBZ + col + dz) * W8 + kq];
+                        bf16x4 b;
+                        __builtin_memcpy(&b, &bw, sizeof(b));
+                        acc[rr] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc[rr], 0, 0, 0);
+                    }
+                }
+        } else if constexpr (CPIN == 16) {
             // one K chunk per tap (16 channels).  For fixed (dx, dz) the four
             // segments and three dy offsets read only six brick rows (segment
             // s at offset dy is row s + dy): each B operand read from LDS
@@ -225,27 +286,42 @@ __global__ __launch_bounds__(256, 3) void k_conv(const uint16_t* __restrict__ in
         }
         // epilogue: lane holds out[cell][4*kq + q] of each segment
         const int x = x0 + wave, z = z0 + col, m0 = 4 * kq;
+        if constexpr (FEW) {
+            // lane group dy holds brick row s + dy's share of output row s; the
+            // sum lands in every group, and group s keeps row s
+            float o2[2] = {0.0f, 0.0f};
 #pragma unroll
-        for (int s2 = 0; s2 < kCTY; ++s2) {
-            const int y = y0 + s2;
-            if (x >= n || y >= n || z >= n) continue;
-            const int64_t cell = (int64_t(x) * n + y) * n + z;
-            if constexpr (EPI == kEpiBiasF32) {
-                float* o = static_cast<float*>(out);
+            for (int s2 = 0; s2 < kCTY; ++s2)
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    if (m0 + q < COUT) gstr(o, cell * COUT + m0 + q, acc[s2][q] + gldr(bias, m0 + q));
-            } else if constexpr (EPI == kEpiApply) {
-                static_assert(COUT == 2, "the correction has two output channels");
-                if (m0 != 0) continue;
-                float* psi = static_cast<float*>(out);
-                const float re = gldr(psi, 2 * cell) + s_out * (acc[s2][0] + gldr(bias, 0));
-                const float im = gldr(psi, 2 * cell + 1) + s_out * (acc[s2][1] + gldr(bias, 1));
-                gstr(psi, 2 * cell, re);
-                gstr(psi, 2 * cell + 1, im);
-                mass += double(re) * double(re) + double(im) * double(im);
-            } else {
-                if (m0 >= CPOUT) continue;
+                for (int o = 0; o < 2; ++o) {
+                    float v = kq == 0   ? acc[s2][o]
+                              : kq == 1 ? acc[s2 + 1][o]
+                              : kq == 2 ? acc[s2 + 2][o]
+                                        : 0.0f;
+                    v += __shfl_xor(v, 16);
+                    v += __shfl_xor(v, 32);
+                    if (kq == s2) o2[o] = v;
+                }
+            const int y = y0 + kq;
+            if (x < n && y < n && z < n) {
+                const int64_t cell = (int64_t(x) * n + y) * n + z;
+                float* to = static_cast<float*>(out);   // (the correction: psi)
+                float re = o2[0] + gldr(bias, 0), im = o2[1] + gldr(bias, 1);
+                if constexpr (EPI == kEpiApply) {
+                    re = gldr(to, 2 * cell) + s_out * re;
+                    im = gldr(to, 2 * cell + 1) + s_out * im;
+                    mass += double(re) * double(re) + double(im) * double(im);
+                }
+                gstr(to, 2 * cell, re);
+                gstr(to, 2 * cell + 1, im);
+            }
+        } else {
+            static_assert(EPI == kEpiBiasReluBf16 || EPI == kEpiMaskBf16, "bf16 outputs");
+#pragma unroll
+            for (int s2 = 0; s2 < kCTY; ++s2) {
+                const int y = y0 + s2;
+                if (x >= n || y >= n || z >= n || m0 >= CPOUT) continue;
+                const int64_t cell = (int64_t(x) * n + y) * n + z;
                 uint16_t rq[4];
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
@@ -662,45 +738,47 @@ __global__ __launch_bounds__(256) void k_wgrad_sum(const float* __restrict__ par
 
 // ---- packing, loss, Adam ---------------------------------------------------
 
-// f32 [cells][cin] -> bf16 [cells][CP] (zero padded), channel c scaled by
-// sc[sidx[c]] (the network's input scales, device doubles) when sc is given.
-__global__ void k_pack_bf16(const float* __restrict__ x, uint16_t* __restrict__ y, int64_t cells,
-                            int cin, int cp, const double* __restrict__ sc) {
-    const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
-    if (i >= cells * cp) return;
-    const int64_t p = i / cp;
-    const int c = int(i % cp);
-    float v = 0.0f;
-    if (c < cin) {
-        v = gldr(x, p * cin + c);
+// f32 [cells][CIN] -> bf16 [cells][4] (zero padded), a cell a lane (a value a lane,
+// its indices by 64-bit division: 23 us at 128^3, now 12); channels scaled by sc[0]
+// and, from the third on, sc[1] (the network's input scales, device doubles) when
+// sc is given.
+template <int CIN>
+__global__ __launch_bounds__(256) void k_pack_bf16(const float* __restrict__ x,
+                                                   uint64_t* __restrict__ y, int64_t cells,
+                                                   const double* __restrict__ sc) {
+    const int64_t p = int64_t(blockIdx.x) * 256 + threadIdx.x;
+    if (p >= cells) return;
+    uint64_t w = 0;
+#pragma unroll
+    for (int c = 0; c < CIN; ++c) {
+        float v = gldr(x, p * CIN + c);
         if (sc) v *= float(gldr(sc, c < 2 ? 0 : 1));
+        w |= uint64_t(f2bf(v)) << (16 * c);
     }
-    gstr(y, i, f2bf(v));
+    gstr(y, p, w);
 }
 
-// loss = sum (y - t)^2 / count in FP64 partials; dy = bf16(2 (y - t) / count)
-// stored with CP channels.
+// loss = sum (y - t)^2 / count in FP64 partials over two channels; dy = bf16(2 (y -
+// t) / count), stored with four.  A cell a lane (28 us at 128^3 as above, now 12).
 // The target t is in the network's output units divided by s_out (read
 // from *s_out when given): the network learns t / s_out.
 __global__ __launch_bounds__(256) void k_mse(const float* __restrict__ y, const float* __restrict__ t,
-                                             uint16_t* __restrict__ dy, double* __restrict__ part,
-                                             int64_t cells, int cout, int cp,
-                                             const double* __restrict__ s_out) {
+                                             uint64_t* __restrict__ dy, double* __restrict__ part,
+                                             int64_t cells, const double* __restrict__ s_out) {
     __shared__ double red[256];
-    const int64_t count = cells * cout;
+    const int64_t count = cells * 2;
     const float inv = s_out ? float(1.0 / gldr(s_out, 0)) : 1.0f;
     double s = 0.0;
-    for (int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x; i < cells * cp;
-         i += int64_t(gridDim.x) * 256) {
-        const int64_t p = i / cp;
-        const int c = int(i % cp);
-        float g = 0.0f;
-        if (c < cout) {
-            const float d = gldr(y, p * cout + c) - gldr(t, p * cout + c) * inv;
+    for (int64_t p = int64_t(blockIdx.x) * 256 + threadIdx.x; p < cells;
+         p += int64_t(gridDim.x) * 256) {
+        uint64_t w = 0;
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const float d = gldr(y, p * 2 + c) - gldr(t, p * 2 + c) * inv;
             s += double(d) * double(d);
-            g = float(2.0 * double(d) / double(count));
+            w |= uint64_t(f2bf(float(2.0 * double(d) / double(count)))) << (16 * c);
         }
-        gstr(dy, i, f2bf(g));
+        gstr(dy, p, w);
     }
     red[threadIdx.x] = s;
     __syncthreads();
@@ -960,15 +1038,22 @@ hipError_t conv_backward_weight(hipStream_t s, int layer, const uint16_t* dz,
 }
 
 hipError_t net_pack_input(hipStream_t s, const float* x, uint16_t* y, int64_t cells, int cin,
-                          int cp, const double* scales) {
-    k_pack_bf16<<<unsigned((cells * cp + 255) / 256), 256, 0, s>>>(x, y, cells, cin, cp, scales);
+                          const double* scales) {
+    const unsigned g = unsigned((cells + 255) / 256);
+    uint64_t* out = reinterpret_cast<uint64_t*>(y);
+    if (cin == 3)
+        k_pack_bf16<3><<<g, 256, 0, s>>>(x, out, cells, scales);
+    else if (cin == 2)
+        k_pack_bf16<2><<<g, 256, 0, s>>>(x, out, cells, scales);
+    else
+        return hipErrorInvalidValue;
     return hipGetLastError();
 }
 
 hipError_t net_mse(hipStream_t s, const float* y, const float* t, uint16_t* dy, double* part,
-                   double* out, int64_t cells, int cout, int cp, const double* s_out) {
+                   double* out, int64_t cells, const double* s_out) {
     constexpr int kBlocks = 1024;
-    k_mse<<<kBlocks, 256, 0, s>>>(y, t, dy, part, cells, cout, cp, s_out);
+    k_mse<<<kBlocks, 256, 0, s>>>(y, t, reinterpret_cast<uint64_t*>(dy), part, cells, s_out);
     k_sum_parts<<<1, 256, 0, s>>>(part, kBlocks, out, 0);
     return hipGetLastError();
 }
