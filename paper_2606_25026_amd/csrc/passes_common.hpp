@@ -336,10 +336,10 @@ __device__ __forceinline__ void write_kinetic_table(const MemberDev& m, double d
 // q % inner and has element stride `st`.
 // ===========================================================================
 // Row pitch of the vacuum solve's padded grid between its z passes: the density
-// is real, so the modes 0..n of a row of 2n suffice; eight elements more than n
-// keep the rows on 64 bytes and their strides off the powers of two.
+// is real, so the modes 0..n of a row of 2n suffice; sixteen elements more than n
+// keep the rows on 128-byte lines and their strides off the powers of two.
 __device__ __host__ __forceinline__ constexpr int vac_pitch(int padded_nz) {
-    return padded_nz / 2 + 8;
+    return padded_nz / 2 + 16;
 }
 
 struct Strides {

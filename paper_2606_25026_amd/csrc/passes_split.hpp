@@ -10,8 +10,8 @@
 //            x, multiplies, and transforms back to (x, y0)
 //   z pass   k1 -> j and z back to real space
 //
-// Per cell the step then moves 24 (P1) + 16 (kinetic plane pass) + 28 (P5) + 8
-// (Green's plane pass) = 76 bytes in four launches instead of 124 in eight:
+// Per cell the step then moves 24 (P1) + 16 (kinetic plane pass) + 24 (P5) + 8
+// (Green's plane pass) = 72 bytes in four launches instead of 120 in eight:
 // the y passes were streams at 6 TB/s with their vector units a third busy, and
 // the butterflies they carried fit beside the other passes' traffic.  Step times
 // without particles, eight against four passes: 16^3 28.7 / 18.7 us, 64^3 40.7 /

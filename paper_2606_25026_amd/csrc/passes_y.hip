@@ -198,7 +198,7 @@ struct RestrictFft {
 // each pencil as zeros (forward) or do not store it (inverse), so the padded
 // grid's y >= ny rows are never touched.  The rows hold the modes 0..nz of a real
 // row's spectrum, vac_pitch elements apart (all 2 nz of them, 19 + 18 + 11 + 11 us
-// for the four and 41 for the x pass at 128^3; now 14 + 15 + 10 + 10 and 28):
+// for the four and 41 for the x pass at 128^3; now 12 + 12 + 10 + 9 and 28):
 //   kVacZFwd  the density rows (real, nz values, held in Phi) zero-extended to
 //             2 nz, forward z transform into the padded rows (x < nx, y < ny);
 //   kVacYFwd  forward y transform of the x < nx pencils, inputs y >= ny zero;
