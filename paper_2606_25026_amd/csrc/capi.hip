@@ -2035,7 +2035,13 @@ wdm_status wdm_restrict(wdm_plan* fine, int32_t fmember, wdm_plan* coarse, int32
     const MemberDev& mc = coarse->host[coarse->dev_index[cmember]];
     const Launch LF = one(fine, fmember), LC = one(coarse, cmember);
     const size_t cs = prec ? 16 : 8;
-    HIPCHK(launch_restrict_fft(LF, prec, f.nx, c.nx, mc.scratch));
+    // members of one plan share its scratch, which the last fine transform still
+    // reads: the coarse spectrum then goes through psi_out
+    const bool shared = LF.members == LC.members;
+    HIPCHK(launch_restrict_fft(LF, prec, f.nx, c.nx, shared ? psi_out : mc.scratch));
+    if (shared)
+        HIPCHK(hipMemcpyAsync(mc.scratch, psi_out, size_t(cells_of(c)) * cs,
+                              hipMemcpyDeviceToDevice, coarse->stream));
     // the last transform writes psi_out, or scratch and a copy if its address is
     // no multiple of an element
     const bool aligned = reinterpret_cast<uintptr_t>(psi_out) % cs == 0;

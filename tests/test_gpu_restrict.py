@@ -39,3 +39,15 @@ def test_restriction_matches_numpy(wdm, nf, nc, prec):
         assert (out[:shift] == 0).all() and (out[shift + 2 * nc ** 3:] == 0).all()
         got = out[shift:shift + 2 * nc ** 3].astype(np.float64).view(np.complex128)
         assert np.linalg.norm(got - ref.ravel()) <= tol * np.linalg.norm(ref)
+
+
+def test_members_of_one_plan(wdm):
+    rng = np.random.default_rng(1)
+    psi = (rng.standard_normal((64,) * 3) + 1j * rng.standard_normal((64,) * 3)).astype(np.complex64)
+    plan = wdm.Plan([wdm.make_config(64), wdm.make_config(32)])
+    wdm.wdm_set_state(plan.handle, 0, torch.from_numpy(psi).cuda())
+    out = torch.empty((32,) * 3, dtype=torch.complex64, device="cuda")
+    wdm.wdm_restrict(plan.handle, 0, plan.handle, 1, out)
+    ref = restricted(psi.astype(np.complex128), 32)
+    tol = 8 * np.log2(64 ** 3) * 2.0 ** -23
+    assert np.linalg.norm(out.cpu().numpy() - ref) <= tol * np.linalg.norm(ref)
