@@ -46,7 +46,7 @@ hipError_t net_moments(hipStream_t s, const float* x, const float* y, int64_t ce
 hipError_t net_fit_scales(hipStream_t s, const double* rows, double count, double* scal);
 hipError_t net_set_scales(hipStream_t s, double* scal, double s_psi, double s_phi, double s_out);
 size_t net_moment_doubles();
-hipError_t launch_shells(const Launch& L, int prec, int nbins, double* part, double* out);
+hipError_t launch_shells(const Launch& L, int prec, int n, int nbins, double* part, double* out);
 hipError_t launch_distance(const Launch& L, int prec, const void* other, int64_t n, double* part,
                            double* out);
 size_t shells_partial_doubles();
@@ -2087,7 +2087,7 @@ wdm_status wdm_power_spectrum(wdm_plan* p, int32_t member, int32_t nbins, double
         HIPCHK(launch_axis_fft(L, p->prec, c.nx, c.ny, c.nz, ax, false, 1));
     double* part = reinterpret_cast<double*>(p->ws + p->layout.pk);
     double* res = part + shells_partial_doubles() - 2 * 1024;
-    HIPCHK(launch_shells(L, p->prec, nbins, part, res));
+    HIPCHK(launch_shells(L, p->prec, c.nx, nbins, part, res));
     std::vector<double> host(2 * size_t(nbins));
     HIPCHK(hipMemcpyAsync(host.data(), res, host.size() * sizeof(double), hipMemcpyDeviceToHost,
                           p->stream));
