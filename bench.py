@@ -244,10 +244,12 @@ def bench_ensemble(args):
     torch.cuda.synchronize()
     el = time.perf_counter() - t0
     ms = el * 1e3 / args.steps
-    # classes whose tuned table is all default step in four passes
+    # classes whose tuned table is all default step in four passes, unless the
+    # eight were chosen for them
     sizes = sorted({m.n for m in members})
-    per_cell = {n: STEP_BYTES_PER_CELL_EIGHT if any(tuning[6 * k:6 * k + 6]) else STEP_BYTES_PER_CELL
-                for k, n in enumerate(sizes)}
+    eight = wdm.wdm_get_step_form(h)
+    per_cell = {n: STEP_BYTES_PER_CELL_EIGHT if eight[k] or any(tuning[6 * k:6 * k + 6])
+                else STEP_BYTES_PER_CELL for k, n in enumerate(sizes)}
     step_bytes = (sum(per_cell[m.n] * m.n ** 3 for m in members)
                   + STEP_BYTES_PER_PARTICLE * parts)
     gbs = step_bytes / (ms * 1e-3) / 1e9
@@ -526,10 +528,12 @@ def main():
         avg_s = dom["total_ms"] / dom["launches"] * 1e-3
         alg = BYTES_PER_CELL[dom["name"]] * n3
         ach = alg / avg_s / 1e9
+        variant = pass_variant(dom["name"], tuning)
+        # (the counters of plan 0 are the four-pass kernels')
+        traffic = None if wdm.wdm_get_step_form(h)[0] else traffic_from_profiles(dom["name"], variant)
         roofline = {"bound": "hbm", "kernel": dom["name"], "achieved": ach,
                     "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": ach / HBM_PEAK_GBS,
-                    "traffic": traffic_from_profiles(dom["name"], pass_variant(dom["name"], tuning)),
-                    "fft_plan_variant": pass_variant(dom["name"], tuning),
+                    "traffic": traffic, "fft_plan_variant": variant,
                     "alg_bytes_per_launch": alg, "avg_launch_us": avg_s * 1e6}
     # what a wdm_step call of K steps carries besides its K steps: the closing
     # half kick (P1's kick-only pass and the particles' closing kick) once per

@@ -306,9 +306,9 @@ wdm_status wdm_set_sort_interval(wdm_plan* plan, int32_t interval);
  * stream (a warm-up launch each, then `reps` rounds, reps in [1, 1000], timing
  * each plan once per round in rotating order, each launch between its own
  * events, on zeroed fields) and leaves the default unless another plan's
- * median is at least 2 % below the default's (then the fastest such plan); a
- * table so chosen replaces the four-pass step only if its eight passes are 2 %
- * faster as a whole.
+ * median is at least 2 % below the default's (then the fastest such plan); the
+ * eight passes so chosen, the defaults among them, replace the four-pass step only
+ * if they are 2 % faster as a whole.
  * It overwrites the members' states: call it before wdm_set_state, or set
  * every state again afterwards (wdm_step returns WDM_ESTATE until then).
  * Synchronises.  All plans give the same results up to rounding.
@@ -318,11 +318,19 @@ wdm_status wdm_set_sort_interval(wdm_plan* plan, int32_t interval);
  * 0 for a null plan).  wdm_get_tuning / wdm_set_tuning copy the table to / from
  * a host array of exactly that length (values 0 to 3, each only where that
  * plan exists for the pass and its axis length, else WDM_EINVAL and nothing
- * changes), e.g. to reuse a cached choice without re-timing. */
+ * changes), e.g. to reuse a cached choice without re-timing.
+ *
+ * wdm_get_step_form / wdm_set_step_form: one int32 per size class (a sixth of
+ * wdm_tuning_entries), 0 (the default) the form that the table stands for as
+ * above, 1 the eight passes also where the table is all 0 (another value is
+ * WDM_EINVAL and nothing changes).  wdm_autotune chooses it and wdm_set_tuning
+ * puts it back to 0: a cached choice is the table, then the forms. */
 wdm_status wdm_autotune(wdm_plan* plan, int32_t reps);
 int32_t wdm_tuning_entries(const wdm_plan* plan);
 wdm_status wdm_get_tuning(wdm_plan* plan, int32_t* out, int32_t n);
 wdm_status wdm_set_tuning(wdm_plan* plan, const int32_t* in, int32_t n);
+wdm_status wdm_get_step_form(wdm_plan* plan, int32_t* out, int32_t n);
+wdm_status wdm_set_step_form(wdm_plan* plan, const int32_t* in, int32_t n);
 
 /* Per-pass timing: while enabled, every kernel launch of wdm_step is
  * bracketed by HIP events on the plan's stream.  wdm_profile_read

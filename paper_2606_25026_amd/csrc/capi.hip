@@ -265,11 +265,12 @@ struct SizeClass {
     bool extended = false;  // some member has a self-interaction or absorbing boundary
     int64_t moving_np = 0;  // most particles of a member whose particles move
     bool vacuum = false;    // isolated Poisson solve (the class's members share the boundary)
+    bool eight = false;     // the eight passes, whatever the plans (wdm_set_step_form)
     // Whether the class steps in four passes: where the grid has them, the
     // Poisson solve is periodic (the padded solve hands over a spectrum of its
-    // own form) and no other FFT plan was chosen for a pass.
+    // own form) and neither the eight passes nor another FFT plan was chosen.
     bool four_passes() const {
-        if (vacuum || !split_supported(nx, ny, nz, count)) return false;
+        if (eight || vacuum || !split_supported(nx, ny, nz, count)) return false;
         for (int v : var)
             if (v != 0) return false;
         return true;
@@ -1246,6 +1247,18 @@ hipError_t tune_step(wdm_plan* p, const Launch& L, const SizeClass& c) {
     return hipSuccess;
 }
 
+// The class's plans and form become those of `to`; a state's half spectrum
+// follows the form of the passes that read it.
+hipError_t choose(wdm_plan* p, SizeClass& c, const SizeClass& to) {
+    if (c.four_passes() != to.four_passes()) {
+        const hipError_t e = launch_spec_form(Launch{p->stream, p->table, c.first, c.count},
+                                              p->prec, c.nx, c.ny, c.nz, to.four_passes());
+        if (e != hipSuccess) return e;
+    }
+    c = to;
+    return hipSuccess;
+}
+
 }  // namespace
 
 int32_t wdm_tuning_entries(const wdm_plan* p) {
@@ -1273,16 +1286,34 @@ wdm_status wdm_set_tuning(wdm_plan* p, const int32_t* in, int32_t n) {
                                         : v == 2 ? "no wide-row plan for this pass and length"
                                                  : "no complex-exchange plan for this pass and length");
         }
-    for (size_t k = 0; k < p->classes.size(); ++k) {
-        SizeClass& c = p->classes[k];
-        const bool four = c.four_passes();
-        for (int j = 0; j < kTuneSlots; ++j) c.var[j] = in[k * kTuneSlots + j];
-        // a state's half spectrum follows the form of the passes that read it
-        if (c.four_passes() != four)
-            HIPCHK(launch_spec_form(Launch{p->stream, p->table, c.first, c.count}, p->prec, c.nx,
-                                    c.ny, c.nz, !four));
-    }
     drop_graphs(p);
+    for (size_t k = 0; k < p->classes.size(); ++k) {
+        SizeClass to = p->classes[k];
+        for (int j = 0; j < kTuneSlots; ++j) to.var[j] = in[k * kTuneSlots + j];
+        to.eight = false;
+        HIPCHK(choose(p, p->classes[k], to));
+    }
+    return WDM_OK;
+}
+
+wdm_status wdm_get_step_form(wdm_plan* p, int32_t* out, int32_t n) {
+    if (!p || !out) return fail(WDM_EINVAL, "null argument");
+    if (n != int32_t(p->classes.size())) return fail(WDM_EINVAL, "n must equal the size classes");
+    for (size_t k = 0; k < p->classes.size(); ++k) out[k] = p->classes[k].eight ? 1 : 0;
+    return WDM_OK;
+}
+
+wdm_status wdm_set_step_form(wdm_plan* p, const int32_t* in, int32_t n) {
+    if (!p || !in) return fail(WDM_EINVAL, "null argument");
+    if (n != int32_t(p->classes.size())) return fail(WDM_EINVAL, "n must equal the size classes");
+    for (int32_t k = 0; k < n; ++k)
+        if (in[k] != 0 && in[k] != 1) return fail(WDM_EINVAL, "step forms are 0 or 1");
+    drop_graphs(p);
+    for (int32_t k = 0; k < n; ++k) {
+        SizeClass to = p->classes[k];
+        to.eight = in[k] != 0;
+        HIPCHK(choose(p, p->classes[k], to));
+    }
     return WDM_OK;
 }
 
@@ -1321,6 +1352,7 @@ wdm_status wdm_autotune(wdm_plan* p, int32_t reps) {
             if (e == hipSuccess) e = launch_zero(p->stream, m.spec_nyq, size_t(c.nx) * c.ny * cs);
             if (e == hipSuccess) e = launch_zero(p->stream, m.dt, 4 * sizeof(double));
         }
+        c.eight = false;
         for (int j = 0; j < kTuneSlots && e == hipSuccess; ++j) {
             c.var[j] = 0;
             int plans[kTunePlans], np = 0;
@@ -1359,10 +1391,13 @@ wdm_status wdm_autotune(wdm_plan* p, int32_t reps) {
                 if (med[i] < (1.0f - kTuneMargin) * med[0] && med[i] < med[best]) best = i;
             c.var[j] = plans[best];
         }
-        // the chosen plans against the four-pass step, as whole sequences
+        // the chosen plans, the defaults among them, against the four-pass step, as
+        // whole sequences
         SizeClass four = c;
         for (int& v : four.var) v = 0;
-        if (e == hipSuccess && !c.four_passes() && four.four_passes()) {
+        four.eight = false;
+        c.eight = c.four_passes();   // (a table of zeros alone means four)
+        if (e == hipSuccess && four.four_passes()) {
             const SizeClass* seq[2] = {&four, &c};
             for (int i = 0; i < 2 && e == hipSuccess; ++i) e = tune_step(p, L, *seq[i]);
             for (int r = 0; r < reps && e == hipSuccess; ++r)

@@ -91,6 +91,8 @@ _SIGS = {
     "wdm_tuning_entries": (_i32, [_vp]),
     "wdm_get_tuning": (C.c_int, [_vp, C.POINTER(_i32), _i32]),
     "wdm_set_tuning": (C.c_int, [_vp, C.POINTER(_i32), _i32]),
+    "wdm_get_step_form": (C.c_int, [_vp, C.POINTER(_i32), _i32]),
+    "wdm_set_step_form": (C.c_int, [_vp, C.POINTER(_i32), _i32]),
     "wdm_profile": (C.c_int, [_vp, _i32]),
     "wdm_profile_read": (C.c_int, [_vp, C.POINTER(wdm_kernel_stat), _i32, C.POINTER(_i32)]),
     "wdm_copy_bandwidth": (C.c_int, [_vp, _vp, C.c_size_t, _i32, _vp, C.POINTER(_f64)]),
@@ -289,6 +291,19 @@ def wdm_set_tuning(plan, table):
     _check(load().wdm_set_tuning(plan, arr, n))
 
 
+def wdm_get_step_form(plan):
+    n = wdm_tuning_entries(plan) // 6
+    out = (_i32 * n)()
+    _check(load().wdm_get_step_form(plan, out, n))
+    return [int(v) for v in out]
+
+
+def wdm_set_step_form(plan, forms):
+    n = len(forms)
+    arr = (_i32 * n)(*[int(v) for v in forms])
+    _check(load().wdm_set_step_form(plan, arr, n))
+
+
 def tuning_key(configs) -> str:
     """Cache key of a plan's tuning table: its distinct grid shapes in the
     order of its size classes, and the precision."""
@@ -300,8 +315,10 @@ def tuning_key(configs) -> str:
 
 def autotune(plan, configs, cache=None, reps=20):
     """Choose the step passes' FFT plans: from the JSON file `cache` when it
-    holds this plan's key, else by wdm_autotune (and store the result there).
-    Overwrites the members' states (set them afterwards).  Returns the table."""
+    holds this plan's key, else by wdm_autotune (and store the result there; the
+    classes that take the eight passes under a table of zeros under a key of
+    their own).  Overwrites the members' states (set them afterwards).  Returns
+    the table."""
     import json
     from pathlib import Path
 
@@ -311,11 +328,16 @@ def autotune(plan, configs, cache=None, reps=20):
         store = json.loads(Path(cache).read_text())
         if key in store and len(store[key]) == wdm_tuning_entries(plan):
             wdm_set_tuning(plan, store[key])
+            wdm_set_step_form(plan, store.get(key + " forms", [0] * (len(store[key]) // 6)))
             return list(store[key])
     wdm_autotune(plan, reps)
     table = wdm_get_tuning(plan)
     if cache is not None:
         store[key] = table
+        forms = wdm_get_step_form(plan)
+        store.pop(key + " forms", None)
+        if any(forms):
+            store[key + " forms"] = forms
         Path(cache).write_text(json.dumps(store, indent=1))
     return table
 
