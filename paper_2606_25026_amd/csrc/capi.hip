@@ -260,6 +260,7 @@ struct SizeClass {
     int first, count;       // device-table range
     int nx, ny, nz;
     int64_t max_np;
+    int prec;
     int var[kTuneSlots] = {0, 0, 0, 0, 0, 0};   // plan variant per tunable pass
     bool absorb = false;    // some member has an absorbing boundary
     bool extended = false;  // some member has a self-interaction or absorbing boundary
@@ -270,7 +271,7 @@ struct SizeClass {
     // Poisson solve is periodic (the padded solve hands over a spectrum of its
     // own form) and neither the eight passes nor another FFT plan was chosen.
     bool four_passes() const {
-        if (eight || vacuum || !split_supported(nx, ny, nz, count)) return false;
+        if (eight || vacuum || !split_supported(nx, ny, nz, count, prec, moving_np > 0)) return false;
         for (int v : var)
             if (v != 0) return false;
         return true;
@@ -655,7 +656,7 @@ wdm_status wdm_plan_create(const wdm_config* members, int32_t n_members, void* w
         if (p->classes.empty() || p->classes.back().nx != c.nx || p->classes.back().ny != c.ny ||
             p->classes.back().nz != c.nz ||
             p->classes.back().vacuum != (c.boundary == WDM_BOUNDARY_VACUUM)) {
-            p->classes.push_back({d, 0, c.nx, c.ny, c.nz, 0});
+            p->classes.push_back({d, 0, c.nx, c.ny, c.nz, 0, p->prec});
             p->classes.back().vacuum = c.boundary == WDM_BOUNDARY_VACUUM;
         }
         p->classes.back().count++;

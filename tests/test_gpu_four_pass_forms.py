@@ -20,15 +20,17 @@ RADIX = {16: (4, 4), 32: (8, 4), 64: (8, 8), 96: (12, 8), 128: (16, 8), 192: (12
          256: (16, 16)}
 SIDES = (16, 32, 64, 96, 128, 192, 256)
 
-FOUR = [(16, 16, 16), (16, 32, 32), (16, 64, 64), (16, 96, 128), (16, 128, 192), (16, 192, 32),
-        (32, 16, 32), (32, 32, 256), (32, 64, 16), (32, 96, 256), (32, 128, 256), (32, 192, 192),
+FOUR = [(16, 16, 16), (16, 32, 32), (16, 64, 128), (16, 96, 128), (16, 128, 192), (16, 192, 32),
+        (32, 16, 32), (32, 32, 256), (32, 64, 64), (32, 96, 256), (32, 128, 256), (32, 192, 192),
         (64, 16, 64), (64, 32, 96), (64, 96, 32), (64, 128, 96), (64, 256, 128), (96, 32, 16),
-        (96, 96, 96), (96, 192, 96), (128, 16, 32), (128, 64, 192), (128, 192, 64), (128, 256, 32),
-        (192, 32, 128), (192, 128, 64), (192, 192, 192), (256, 32, 192), (256, 64, 96),
+        (96, 96, 96), (96, 192, 96), (128, 32, 64), (128, 64, 192), (128, 192, 64), (128, 256, 32),
+        (192, 32, 192), (192, 128, 64), (192, 192, 192), (256, 32, 192), (256, 64, 96),
         (256, 128, 128), (256, 256, 32)]
 # too few plane tiles; a pair (nz, R1) that is not built; a side that is not
 EIGHT = [(192, 32, 32), (256, 32, 16), (256, 64, 32), (96, 256, 32), (192, 192, 32), (16, 256, 16),
-         (32, 96, 16), (16, 16, 256), (32, 384, 32), (384, 32, 32)]
+         (32, 96, 16), (16, 16, 256), (32, 384, 32), (384, 32, 32), (192, 192, 128)]
+# the form depends on the precision: four passes in complex64 alone
+SINGLE = [(128, 16, 32), (192, 32, 128), (192, 192, 96), (96, 192, 128)]
 
 
 def test_boxes_reach_every_kernel():
@@ -45,7 +47,7 @@ def rel_l2(a, b):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("prec", [0, 1])
-@pytest.mark.parametrize("n", FOUR + EIGHT, ids=lambda n: "x".join(map(str, n)))
+@pytest.mark.parametrize("n", FOUR + EIGHT + SINGLE, ids=lambda n: "x".join(map(str, n)))
 def test_form_and_result(wdm, orc, n, prec):
     rng = np.random.default_rng(sum(n))
     L = (1.0, 0.75, 1.25)
@@ -61,8 +63,9 @@ def test_form_and_result(wdm, orc, n, prec):
     wdm.wdm_step(plan.handle, 3, dt)
     names = {s["name"] for s in wdm.wdm_profile_read(plan.handle)}
     wdm.wdm_profile(plan.handle, False)
-    assert ({"xy_kinetic", "xy_green"} <= names) == (n in FOUR), names
-    assert ({"x_kinetic", "x_green"} <= names) == (n in EIGHT), names
+    four = n in FOUR or (n in SINGLE and prec == 0)
+    assert ({"xy_kinetic", "xy_green"} <= names) == four, names
+    assert ({"x_kinetic", "x_green"} <= names) == (not four), names
     out = torch.empty_like(x)
     wdm.wdm_get_psi(plan.handle, 0, out)
     got = out.cpu().numpy().astype(np.complex128)
@@ -71,3 +74,18 @@ def test_form_and_result(wdm, orc, n, prec):
     ref = orc.kdk(orc.make_config(n, L=L, four_pi_G=g), start, nsteps=3, dt=dt)[0]
     assert rel_l2(ref, start) > 0.1
     assert rel_l2(got, ref) < TOL[prec]
+
+
+@pytest.mark.gpu
+def test_particles_raise_the_tile_rule(wdm):
+    n = (192, 32, 128)     # 64 tiles: four passes without moving particles alone
+    pos = torch.rand((500, 3), generator=torch.Generator().manual_seed(1)).cuda()
+    psi = torch.ones(n, dtype=torch.complex64, device="cuda")
+    for mode in (wdm.WDM_BARYON_DYNAMIC, wdm.WDM_BARYON_STATIC):
+        plan = wdm.Plan(wdm.make_config(n, n_particles=500, particle_mass=1e-6, baryon_mode=mode))
+        wdm.wdm_set_state(plan.handle, 0, psi, pos, torch.zeros_like(pos))
+        wdm.wdm_profile(plan.handle, True)
+        wdm.wdm_step(plan.handle, 1, 1e-6)
+        names = {s["name"] for s in wdm.wdm_profile_read(plan.handle)}
+        assert ("xy_kinetic" in names) == (mode == wdm.WDM_BARYON_STATIC)
+        plan.close()
