@@ -2071,16 +2071,22 @@ wdm_status wdm_restrict(wdm_plan* fine, int32_t fmember, wdm_plan* coarse, int32
     const MemberDev& mc = coarse->host[coarse->dev_index[cmember]];
     const Launch LF = one(fine, fmember), LC = one(coarse, cmember);
     const size_t cs = prec ? 16 : 8;
+    // kernels write psi_out where its address is a multiple of an element, copies
+    // otherwise
+    const bool aligned = reinterpret_cast<uintptr_t>(psi_out) % cs == 0;
     // members of one plan share its scratch, which the last fine transform still
     // reads: the coarse spectrum then goes through psi_out
     const bool shared = LF.members == LC.members;
-    HIPCHK(launch_restrict_fft(LF, prec, f.nx, c.nx, shared ? psi_out : mc.scratch));
+    HIPCHK(launch_restrict_fft(LF, prec, f.nx, c.nx,
+                               !shared ? mc.scratch : aligned ? psi_out : nullptr));
+    if (shared && !aligned) {
+        const size_t plane = size_t(c.ny) * c.nz * cs;
+        HIPCHK(hipMemcpy2DAsync(psi_out, plane, mc.scratch, size_t(f.nx) * c.nz * cs, plane, c.nx,
+                                hipMemcpyDeviceToDevice, fine->stream));
+    }
     if (shared)
         HIPCHK(hipMemcpyAsync(mc.scratch, psi_out, size_t(cells_of(c)) * cs,
                               hipMemcpyDeviceToDevice, coarse->stream));
-    // the last transform writes psi_out, or scratch and a copy if its address is
-    // no multiple of an element
-    const bool aligned = reinterpret_cast<uintptr_t>(psi_out) % cs == 0;
     for (int ax = 0; ax < 3; ++ax)
         HIPCHK(launch_axis_fft(LC, prec, c.nx, c.ny, c.nz, ax, true, 1,
                                aligned && ax == 2 ? psi_out : nullptr));

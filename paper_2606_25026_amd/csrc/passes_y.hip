@@ -130,7 +130,8 @@ struct ZFftFrom {
 // Forward transforms of psi that keep only the modes |m| < nc/2 of an axis (zero
 // on the coarse Nyquist plane), for the restriction of an N^3 grid: along z from
 // psi into scratch [N][N][nc], along y in place into its first nc rows, along x
-// into the coarse spectrum out [nc][nc][nc], times scale.  A pencil that ends in
+// into the coarse spectrum out [nc][nc][nc] (in place into the first nc planes where
+// out is null), times scale.  A pencil that ends in
 // dropped modes is never formed: at 256 -> 128 the three move 350 MB where full
 // transforms, the copy of psi and a gather of the kept modes moved 1.1 GB (195 ->
 // 67 us).
@@ -157,8 +158,9 @@ __global__ __launch_bounds__((wg_size<typename PlanFor<N>::type, T>())) void k_r
     load_slots<FP, FP::first()>(v, in, b, st, ok, ln);
     pencil_fft<FP, false, T>(v, lds, tw, ln.t, ln);
     if (!ok) return;
-    cplx<T>* to = AXIS == 0 ? out : static_cast<cplx<T>*>(m.scratch);
-    const int64_t ob = AXIS == 2 ? qq * nc : b, ost = AXIS == 0 ? int64_t(nc) * nc : st;
+    const bool dense = AXIS == 0 && out != nullptr;
+    cplx<T>* to = dense ? out : static_cast<cplx<T>*>(m.scratch);
+    const int64_t ob = AXIS == 2 ? qq * nc : b, ost = dense ? int64_t(nc) * nc : st;
 #pragma unroll
     for (int s = 0; s < FP::E; ++s) {
         const int e = slot_elem<FP, FP::last()>(ln.t, s);

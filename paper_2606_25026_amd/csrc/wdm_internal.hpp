@@ -181,7 +181,8 @@ hipError_t launch_spec_form(const Launch& L, int prec, int nx, int ny, int nz, b
 hipError_t launch_axis_fft(const Launch& L, int prec, int nx, int ny, int nz, int axis,
                            bool inverse, int which, void* z_out = nullptr);
 // The modes of psi (nf^3) that an nc^3 grid resolves, / nf^3, into out [nc][nc][nc]
-// (zero on its Nyquist planes), through scratch; one member.
+// (zero on its Nyquist planes), through scratch; one member.  out null: plane x of
+// the result stays in scratch, x nf nc elements from its start.
 hipError_t launch_restrict_fft(const Launch& L, int prec, int nf, int nc, void* out);
 // Forward z transform into scratch of psi (kFromPsi) or of its density contrast
 // |psi|^2 n / sum|psi|^2 - 1 (kFromContrast; the FP64 sum is results[0]).
