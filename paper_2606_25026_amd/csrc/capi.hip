@@ -835,12 +835,16 @@ hipError_t enqueue_step(wdm_plan* p, hipStream_t s, hipStream_t aux, KickMode km
         // kinetic plane pass, or P2-P4) on the auxiliary stream.  A replayed
         // graph keeps the branch enqueued first on the launching queue and P5
         // waits on the other one across queues, so the branch expected to take
-        // longer goes first (measured with P2-P4 at 10^6 particles: the
-        // particles at 128^3, 0.118 against 0.121 ms per step, the psi passes at
-        // 256^3, 0.408 against 0.410).  The kernels take about 46 ns per 1000
-        // particles, 4.2 ns per 1000 cells for the plane pass and 8 for P2-P4.
-        const bool parts_first =
-            c.moving_np * (four ? 11 : 6) > int64_t(c.nx) * c.ny * c.nz;
+        // longer goes first, the particles then with twice the work-groups.  Step
+        // times in us, psi / particles first.  Four passes: 64^3 + 3e4 46.7 / 43.8,
+        // 96^3 + 1e5 68.3 / 68.6, 128^3 + 1e5 74.2 / 74.2, + 2e5 77.4 / 75.6, + 1e6 94.1 /
+        // 88.9; from 2^22 cells on psi exceeds the XCDs' L2s and the plane pass takes
+        // longer for its size: 192^3 + 6e5 192 / 202, + 1e6 199 / 199, + 2e6 226 / 220,
+        // 256^3 + 1e6 329 / 338, + 2e6 358 / 372 (complex128: 128^3 + 1e5 108.2 / 105.5,
+        // 192^3 + 1e6 352 / 367, 256^3 + 2e6 687 / 682).  Eight passes: 128^3 + 1e6 121 /
+        // 118, 256^3 + 1e6 408 / 410.
+        const int64_t cells = int64_t(c.nx) * c.ny * c.nz;
+        const bool parts_first = c.moving_np * (!four ? 6 : cells < (1 << 22) ? 11 : 7) > cells;
         auto psi_f = [&] {
             if (four)
                 return chk(timed(p, kKXYKin, [&] {
