@@ -280,8 +280,9 @@ wdm_status wdm_fft3d(wdm_plan* plan, int32_t member, int32_t inverse);
 wdm_status wdm_fft3d_noalloc(const void* psi_in, void* psi_out, int32_t nx, int32_t ny, int32_t nz,
                              int32_t precision, int32_t inverse, void* hip_stream);
 
-/* Replay captured HIP graphs of the merged step where that is faster: runs of
- * more than two steps with moving particles (default on).  Otherwise, and off,
+/* Replay captured HIP graphs where that is faster: of the merged step in runs of
+ * more than two steps with moving particles, and of a whole block of steps with
+ * its correction where a corrector is attached (default on).  Otherwise, and off,
  * every kernel is launched directly on the plan's stream.  Results are the same
  * either way; profiling always launches directly. */
 wdm_status wdm_use_graphs(wdm_plan* plan, int32_t enable);

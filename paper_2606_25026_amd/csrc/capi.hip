@@ -485,7 +485,6 @@ wdm_status stability_status(const wdm_config& c, const double stab[2]) {
     return WDM_OK;
 }
 
-// The stability checks of a member's steps so far (synchronises the stream).
 // A member's time step, reductions and stability record behind the work queued
 // so far: one copy of the fields that the layout keeps next to each other, one
 // wait; the state's stability is judged on it.

@@ -31,28 +31,6 @@ __device__ __forceinline__ uint16_t f2bf(float f) {
 }
 __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float(uint32_t(h) << 16); }
 
-// 4 consecutive bf16 values (8-byte aligned) from global memory
-__device__ __forceinline__ bf16x4 ld_bf16x4(const uint16_t* p, int64_t i) {
-    return *((const WDM_GAS bf16x4*)(p + i));
-}
-
-struct Grid3 {
-    int n;   // cubic grid edge
-    __device__ __forceinline__ int64_t cells() const { return int64_t(n) * n * n; }
-    // neighbour of linear cell p at tap t (offsets (t/9-1, (t/3)%3-1, t%3-1)), periodic
-    __device__ __forceinline__ int64_t shift(int64_t p, int t) const {
-        const int64_t nn = int64_t(n) * n;
-        int x = int(p / nn), y = int((p / n) % n), z = int(p % n);
-        x += t / 9 - 1;
-        y += (t / 3) % 3 - 1;
-        z += t % 3 - 1;
-        x = x < 0 ? x + n : (x >= n ? x - n : x);
-        y = y < 0 ? y + n : (y >= n ? y - n : y);
-        z = z < 0 ? z + n : (z >= n ? z - n : z);
-        return (int64_t(x) * n + y) * n + z;
-    }
-};
-
 // Epilogue modes of the convolution kernel.
 enum ConvEpi : int {
     kEpiBiasReluBf16 = 0,   // out = bf16(relu(acc + bias)), CPOUT channels
@@ -965,9 +943,10 @@ __global__ void k_set_scales(double* __restrict__ scal, double s_psi, double s_p
 // host launchers
 // ---------------------------------------------------------------------------
 // Persistent grid of the convolution: one work-group per tile up to `per_cu`
-// per compute unit.  Eight at 4 input channels; three at 16, although their
-// 34.8 KB of LDS and 72-76 VGPRs would allow four: at 128^3 the forward pass
-// measured 155-158 us with three per CU, 170-176 us with four or with two.
+// per compute unit.  Eight at 4 input channels; three at 16, what their 146 to 150
+// VGPRs hold (34.7 KB of LDS would hold four): at 128^3 the forward pass takes 129 us
+// and its 16 -> 16 layer 57, 66 with four launched per CU, the fourth of which waits
+// until another ends.
 static unsigned conv_blocks(int n, int per_cu) {
     static int cus = 0;
     if (cus == 0) {

@@ -22,7 +22,7 @@ __device__ __forceinline__ double diag_block_sum(double v, double* red) {
 }
 
 // |psi| and 1 / |psi|^2 in FP64.  From complex64 the square lies between 2^-298
-// and 2^256, where the reciprocal square root needs no scaling: Goldschmidt's
+// and 2^257, where the reciprocal square root needs no scaling: Goldschmidt's
 // iteration gives both from one, within 2 ulps (zero and infinity apart).
 struct Amp {
     double a, inv;
