@@ -271,7 +271,7 @@ struct SizeClass {
     // Poisson solve is periodic (the padded solve hands over a spectrum of its
     // own form) and neither the eight passes nor another FFT plan was chosen.
     bool four_passes() const {
-        if (eight || vacuum || !split_supported(nx, ny, nz, count, prec, moving_np > 0)) return false;
+        if (eight || vacuum || !split_supported(nx, ny, nz, count, prec, moving_np)) return false;
         for (int v : var)
             if (v != 0) return false;
         return true;

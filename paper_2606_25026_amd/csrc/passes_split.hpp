@@ -81,34 +81,37 @@ constexpr bool plane_supported(int nx, int r2) {
 }
 // Values of z in a tile.
 constexpr int plane_zc(int r2, int nz) { return r2 == 16 ? 4 : r2 == 8 ? 8 : nz >= 32 ? 16 : 8; }
-// Tiles (of all the class's members) below which the eight passes are faster:
-// a tile lasts 15-30 us however few there are, the three passes it replaces
-// about 6 us each on a small grid.  Step times, eight against four passes, in
-// complex64 without particles: nx = 256, 64 tiles 63.2 / 63.5 us (256x64x64), 32 tiles
-// 49.1 / 57.3, 96 tiles 87.4 / 77.9; nx = 192, 16 tiles 45.6 / 46.7, 64 tiles 63.3 / 59.4;
-// the 48 values a lane of nx = 96 and 192 at R2 = 16, 256 tiles 100.5 / 113.7
-// (192x256x64), 288 tiles 100.9 / 90.6 (96x192x96); nx = 128, 16 tiles 41.4 / 36.5; smaller
-// nx are faster at any size (32x16x32: 37.7 / 25.3).
-// Few tiles hide less where a lane's values are doubles or moving particles share
-// the machine: nx = 192, 64 tiles and 10^5 particles 70.9 / 74.3 (192x32x128) and, in
-// complex128, 85.2 / 91.7 (192x64x64; 76.1 / 74.6 without); complex128, nx = 128, 8 tiles
-// 39.1 / 40.4, with 10^4 particles 56.4 / 60.8 (128x16x32), 16 tiles 41.7 / 42.6, 24 tiles
-// 45.9 / 44.5; nx = 96, 16 tiles 40.7 / 40.4, with 10^4 58.0 / 59.5 (96x16x64).
+// Whether the four passes are the faster form for a class with `tiles` plane tiles
+// (of all its members) and up to `np` moving particles a member.  A tile lasts 15-30
+// us however few there are, the three passes it replaces about 6 us each on a small
+// grid.  Step times, eight against four passes, in complex64 without particles:
+// nx = 256, 64 tiles 63.2 / 63.5 us (256x64x64), 32 tiles 49.1 / 57.3, 96 tiles 87.4 /
+// 77.9; nx = 192, 16 tiles 45.6 / 46.7, 64 tiles 63.3 / 59.4; the 48 values a lane of
+// nx = 96 and 192 at R2 = 16, 256 tiles 100.5 / 113.7 (192x256x64), 288 tiles 100.9 / 90.6
+// (96x192x96); nx = 128, 16 tiles 41.4 / 36.5; smaller nx are faster at any size
+// (32x16x32: 37.7 / 25.3).
+// In complex128 few tiles hide less, above all beside many particles: nx = 192, 64
+// tiles (192x64x64) 76.1 / 74.6, with 10^5 particles 84 / 92, with 10^6 107 / 113, but with
+// 10^4 98 / 94 (192x32x128); nx = 128, 8 tiles (128x16x32) 39.1 / 40.4, with 10^4 57 / 61,
+// with 10^6 77 / 81, though with 10^5 65 / 61; 16 tiles (128x32x32) 42.4 / 42.7, with 10^5 67 /
+// 63.
 // Where those 48 values meet z groups of R1 = 12 rows (ny = 192) the four passes need
 // more, the more so the shorter the rows (at nz = 128 a group's columns also leave a
 // third of its lanes idle).  complex64, 192x192x128: 128.6 / 137.4 with 384 tiles, 213.8
 // / 190.9 with 768.  complex128, one, two and three members: 192x192x96 176.5 / 183.8,
-// 294.1 / 317.3, 420 / 426, 192x192x128 214 / 228, 378 / 400, 565 / 619, but 192^3 307.5 /
-// 307.2, 588 / 578, 913 / 841; 96x192x128 138 / 137, 211 / 211, 290 / 318, but 96x192x96
+// 294 / 317, 420 / 426 (with 10^6 particles each 216 / 228, 391 / 420, 581 / 602), 192x192x128
+// 214 / 228, 378 / 400, 565 / 619, but 192^3 307.5 / 307.2, 588 / 578, 913 / 841; 96x192x128
+// 138 / 137, 211 / 211, 290 / 318 (with 10^5 159 / 155, 240 / 228, 336 / 349), but 96x192x96
 // 123.7 / 108.8 and 96x192x192 181 / 170.
-constexpr int plane_min_tiles(int nx, int r1, int r2, int nz, bool c128, bool moving) {
+constexpr bool plane_pays(int nx, int r1, int r2, int nz, int64_t tiles, bool c128, int64_t np) {
     if (r2 == 16 && (nx == 96 || nx == 192)) {
-        if (c128 && r1 == 12 && (nx == 192 ? nz <= 128 : nz == 128)) return 1 << 30;
-        return !c128 && r1 == 12 && nx == 192 && nz == 128 ? 768 : 288;
+        if (r1 == 12 && nx == 192 && nz <= 128 && (c128 || nz == 128)) return !c128 && tiles >= 768;
+        if (r1 == 12 && nx == 96 && nz == 128 && c128) return tiles >= 288 && tiles <= 768;
+        return tiles >= 288;
     }
-    if (nx == 256) return 96;
-    if (nx == 192) return c128 || moving ? 96 : 64;
-    return c128 && (nx == 96 || nx == 128) && nz >= 32 ? 24 : 1;
+    if (nx == 256) return tiles >= 96;
+    if (nx == 192) return tiles >= (c128 && np >= 50000 ? 96 : 64);
+    return !(c128 && nx == 128 && nz >= 32 && tiles < 16);
 }
 // Pairs (nz, R1) that have z passes.
 constexpr bool zrows_supported(int nz, int r1) {

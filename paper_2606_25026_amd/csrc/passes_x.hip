@@ -368,12 +368,12 @@ WDM_SPLIT_DECL(c64)
 WDM_SPLIT_DECL(c128)
 #undef WDM_SPLIT_DECL
 
-bool split_supported(int nx, int ny, int nz, int members, int prec, bool moving) {
+bool split_supported(int nx, int ny, int nz, int members, int prec, int64_t moving_np) {
     const int r1 = y_radix(ny);
     if (r1 == 0 || !zrows_supported(nz, r1) || !plane_supported(nx, ny / r1)) return false;
     const int r2 = ny / r1;
-    return int64_t(members) * r1 * (nz / plane_zc(r2, nz)) >=
-           plane_min_tiles(nx, r1, r2, nz, prec != 0, moving);
+    const int64_t tiles = int64_t(members) * r1 * (nz / plane_zc(r2, nz));
+    return plane_pays(nx, r1, r2, nz, tiles, prec != 0, moving_np);
 }
 hipError_t launch_zy_kick(const Launch& L, int prec, int nx, int ny, int nz, ZOp op, KickMode kick,
                           bool extended) {

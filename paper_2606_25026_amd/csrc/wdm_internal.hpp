@@ -161,10 +161,10 @@ hipError_t launch_z_density(const Launch& L, int prec, int nx, int ny, int nz, D
 // P7: x forward, Green's function -4 pi G / |k|^2 / N, x inverse (+ Nyquist plane).
 hipError_t launch_x_green(const Launch& L, int prec, int nx, int ny, int nz, int variant = 0);
 // ---- four-pass step (passes_split.hpp; passes_zy_*.hip, passes_xy_*.hip) ----
-// Whether a class of members of this grid and precision, with or without moving
-// particles, takes it (P1, the kinetic plane pass, P5 and the Green's plane pass in
-// place of P1 - P8).
-bool split_supported(int nx, int ny, int nz, int members, int prec, bool moving);
+// Whether a class of members of this grid and precision, with up to moving_np moving
+// particles each, takes it (P1, the kinetic plane pass, P5 and the Green's plane pass
+// in place of P1 - P8).
+bool split_supported(int nx, int ny, int nz, int members, int prec, int64_t moving_np);
 // P1 (kZKickFft, kZKickOnly, kZPhiOnly), P5 (kDensInvFft, kDensDirect) and the
 // plane passes; the half spectrum is in the (y0, k1) form between them.
 hipError_t launch_zy_kick(const Launch& L, int prec, int nx, int ny, int nz, ZOp op, KickMode kick,

@@ -23,14 +23,14 @@ SIDES = (16, 32, 64, 96, 128, 192, 256)
 FOUR = [(16, 16, 16), (16, 32, 32), (16, 64, 128), (16, 96, 128), (16, 128, 192), (16, 192, 32),
         (32, 16, 32), (32, 32, 256), (32, 64, 64), (32, 96, 256), (32, 128, 256), (32, 192, 192),
         (64, 16, 64), (64, 32, 96), (64, 96, 32), (64, 128, 96), (64, 256, 128), (96, 32, 16),
-        (96, 96, 96), (96, 192, 96), (128, 32, 64), (128, 64, 192), (128, 192, 64), (128, 256, 32),
-        (192, 32, 192), (192, 128, 64), (192, 192, 192), (256, 32, 192), (256, 64, 96),
+        (96, 96, 96), (96, 192, 96), (96, 192, 128), (128, 32, 32), (128, 64, 192), (128, 192, 64), (128, 256, 32),
+        (192, 32, 128), (192, 128, 64), (192, 192, 192), (256, 32, 192), (256, 64, 96),
         (256, 128, 128), (256, 256, 32)]
 # too few plane tiles; a pair (nz, R1) that is not built; a side that is not
 EIGHT = [(192, 32, 32), (256, 32, 16), (256, 64, 32), (96, 256, 32), (192, 192, 32), (16, 256, 16),
          (32, 96, 16), (16, 16, 256), (32, 384, 32), (384, 32, 32), (192, 192, 128)]
 # the form depends on the precision: four passes in complex64 alone
-SINGLE = [(128, 16, 32), (192, 32, 128), (192, 192, 96), (96, 192, 128)]
+SINGLE = [(128, 16, 32), (192, 192, 96)]
 
 
 def test_boxes_reach_every_kernel():
@@ -78,14 +78,32 @@ def test_form_and_result(wdm, orc, n, prec):
 
 @pytest.mark.gpu
 def test_particles_raise_the_tile_rule(wdm):
-    n = (192, 32, 128)     # 64 tiles: four passes without moving particles alone
-    pos = torch.rand((500, 3), generator=torch.Generator().manual_seed(1)).cuda()
-    psi = torch.ones(n, dtype=torch.complex64, device="cuda")
-    for mode in (wdm.WDM_BARYON_DYNAMIC, wdm.WDM_BARYON_STATIC):
-        plan = wdm.Plan(wdm.make_config(n, n_particles=500, particle_mass=1e-6, baryon_mode=mode))
+    n = (192, 32, 128)     # 64 tiles: in complex128 eight passes beside many moving particles
+    pos = torch.rand((50_000, 3), generator=torch.Generator().manual_seed(1)).cuda()
+    psi = torch.ones(n, dtype=torch.complex128, device="cuda")
+    for npart, mode, four in ((50_000, wdm.WDM_BARYON_DYNAMIC, False),
+                              (49_999, wdm.WDM_BARYON_DYNAMIC, True),
+                              (50_000, wdm.WDM_BARYON_STATIC, True)):
+        plan = wdm.Plan(wdm.make_config(n, n_particles=npart, particle_mass=1e-6, precision=1,
+                                        baryon_mode=mode))
         wdm.wdm_set_state(plan.handle, 0, psi, pos, torch.zeros_like(pos))
         wdm.wdm_profile(plan.handle, True)
         wdm.wdm_step(plan.handle, 1, 1e-6)
         names = {s["name"] for s in wdm.wdm_profile_read(plan.handle)}
-        assert ("xy_kinetic" in names) == (mode == wdm.WDM_BARYON_STATIC)
+        assert ("xy_kinetic" in names) == four
+        plan.close()
+
+
+@pytest.mark.gpu
+def test_members_count_in_the_tile_rule(wdm):
+    n = (96, 192, 128)     # 384 tiles a member: in complex128 four passes up to 768
+    for members, four in ((2, True), (3, False)):
+        plan = wdm.Plan([wdm.make_config(n, precision=1)] * members)
+        psi = torch.ones(n, dtype=torch.complex128, device="cuda")
+        for k in range(members):
+            wdm.wdm_set_state(plan.handle, k, psi)
+        wdm.wdm_profile(plan.handle, True)
+        wdm.wdm_step(plan.handle, 1, 1e-6)
+        names = {s["name"] for s in wdm.wdm_profile_read(plan.handle)}
+        assert ("xy_kinetic" in names) == four
         plan.close()
