@@ -838,12 +838,14 @@ hipError_t enqueue_step(wdm_plan* p, hipStream_t s, hipStream_t aux, KickMode km
         // times in us, psi / particles first.  Four passes: 64^3 + 3e4 46.7 / 43.8,
         // 96^3 + 1e5 68.3 / 68.6, 128^3 + 1e5 74.2 / 74.2, + 2e5 77.4 / 75.6, + 1e6 94.1 /
         // 88.9; from 2^22 cells on psi exceeds the XCDs' L2s and the plane pass takes
-        // longer for its size: 192^3 + 6e5 192 / 202, + 1e6 199 / 199, + 2e6 226 / 220,
-        // 256^3 + 1e6 329 / 338, + 2e6 358 / 372 (complex128: 128^3 + 1e5 108.2 / 105.5,
-        // 192^3 + 1e6 352 / 367, 256^3 + 2e6 687 / 682).  Eight passes: 128^3 + 1e6 121 /
-        // 118, 256^3 + 1e6 408 / 410.
+        // longer for its size: 192^3 + 7e5 195 / 201, + 1e6 199 / 199 (spread over the box
+        // instead of clustered 383 / 369), + 2e6 226 / 220, 256^3 + 1e6 329 / 338, + 2e6
+        // 358 / 372 (spread 776 / 799).  In complex128 twice as long: 128^3 + 1e5 108.2 /
+        // 105.5, 192^3 + 1e6 352 / 367 (spread 567 / 592), + 2e6 397 / 403, 256^3 + 2e6 687 /
+        // 682 (spread 1151 / 1144).  Eight passes: 128^3 + 1e6 121 / 118, 256^3 + 1e6 408 / 410.
         const int64_t cells = int64_t(c.nx) * c.ny * c.nz;
-        const bool parts_first = c.moving_np * (!four ? 6 : cells < (1 << 22) ? 11 : 7) > cells;
+        const int line = !four ? 6 : cells < (1 << 22) ? 11 : prec ? 4 : 8;
+        const bool parts_first = c.moving_np * line > cells;
         auto psi_f = [&] {
             if (four)
                 return chk(timed(p, kKXYKin, [&] {
